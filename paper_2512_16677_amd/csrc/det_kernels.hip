@@ -10,6 +10,8 @@
 // matrices.  5 <= n <= 32: one wavefront per matrix, LU with partial
 // pivoting in LDS (lanes over rows), det = sign * prod(U_kk), and
 // adj = det * A^{-1} from substitutions (lanes over columns of A^{-1}).
+#include <type_traits>
+
 #include "qmk_internal.h"
 
 namespace qmk {
@@ -95,27 +97,41 @@ __global__ __launch_bounds__(256) void det_adj_small_kernel(const double* __rest
   for (int64_t e = threadIdx.x; e < nb * E; e += 256) dst[e] = s_m[(e / E) * LD + e % E];
 }
 
-// One wavefront per matrix, 4 per workgroup; n <= 32.
-__global__ __launch_bounds__(256) void det_adj_lu_kernel(const double* __restrict__ A, int n, int64_t batch,
-                                                         double* __restrict__ det,
-                                                         double* __restrict__ adj) {
-  __shared__ double s_lu[4][32][33];
-  __shared__ int s_piv[4][32];
-  __shared__ double s_a[4][32], s_r[4][32];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t b = static_cast<int64_t>(blockIdx.x) * 4 + w;
-  if (b >= batch) return;  // whole waves leave together; no workgroup barrier below
-  double(*lu)[33] = s_lu[w];
-  const double* src = A + b * n * n;
-  for (int e = lane; e < n * n; e += 64) lu[e / n][e % n] = src[e];
+// Orders the LDS accesses of one wavefront's lanes (its part of the LDS is
+// its own).
+__device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS of one wavefront for the LU of one N x N matrix and the solves.
+template <int N>
+struct LuLds {
+  double lu[N][33];
+  double x[N][33];  // column `lane` of A^{-1}
+  double a[N], r[N];
+  int piv[N];
+};
+
+// One matrix by the whole wavefront: LU with partial pivoting in LDS (lanes
+// over rows), adj = det * A^{-1} from substitutions (lanes over columns), and
+// the singular cases.
+template <int N>
+__device__ void lu_general(const double* __restrict__ src, double* __restrict__ det, double* __restrict__ dst,
+                           int lane, LuLds<N>& L) {
+  double(*lu)[33] = L.lu;
+  wave_lds_sync();  // the LDS is shared with the caller's staging
+#pragma unroll 1
+  for (int e = lane; e < N * N; e += 64) lu[e / N][e % N] = src[e];
+  wave_lds_sync();
   double sign = 1.0, d = 1.0;
-  for (int k = 0; k < n; ++k) {
+#pragma unroll 1
+  for (int k = 0; k < N; ++k) {
     // pivot: largest |a_ik|, i >= k (ties to the lowest row)
-    double v = lane >= k && lane < n ? fabs(lu[lane][k]) : -1.0;
+    double v = lane >= k && lane < N ? fabs(lu[lane][k]) : -1.0;
     int idx = lane;
+#pragma unroll 1
     for (int off = 32; off > 0; off >>= 1) {
       const double ov = __shfl_xor(v, off, 64);
       const int oi = __shfl_xor(idx, off, 64);
@@ -124,33 +140,33 @@ __global__ __launch_bounds__(256) void det_adj_lu_kernel(const double* __restric
         idx = oi;
       }
     }
-    const int p = idx;
-    if (lane == 0) s_piv[w][k] = p;
+    // (with NaN entries the lanes may disagree: one of them decides, and where
+    // it knows of no row but NaN ones, row k stays)
+    int p = __builtin_amdgcn_readfirstlane(idx);
+    if (p < k || p >= N) p = k;
+    if (lane == 0) L.piv[k] = p;
     if (p != k) {
-      if (lane < n) {
+      if (lane < N) {
         const double t = lu[k][lane];
         lu[k][lane] = lu[p][lane];
         lu[p][lane] = t;
       }
       sign = -sign;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_sync();
     const double piv = lu[k][k];
     d *= piv;
-    if (lane > k && lane < n) {
+    if (lane > k && lane < N) {
       // a zero pivot leaves only zeros below it: nothing to eliminate
       const double l = piv != 0.0 ? lu[lane][k] / piv : 0.0;
       lu[lane][k] = l;
-      for (int j = k + 1; j < n; ++j) lu[lane][j] -= l * lu[k][j];
+#pragma unroll 1
+      for (int j = k + 1; j < N; ++j) lu[lane][j] -= l * lu[k][j];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_sync();
   }
   d *= sign;
-  if (lane == 0) det[b] = d;
+  if (lane == 0) *det = d;
   // Exactly zero pivots make d A^{-1} undefined; the adjugate is still the
   // transposed cofactor matrix.  With PA = LU, adj(A) = adj(U) L^{-1} sign P.
   // Two or more zero pivots (rank <= n - 2): adj(A) = 0.  One, at k0 (rank
@@ -158,81 +174,254 @@ __global__ __launch_bounds__(256) void det_adj_lu_kernel(const double* __restric
   // cofactor), U a = 0, a_k0 = 1, a_m = 0 past k0, and b^T U = 0, b_k0 = 1,
   // b_m = 0 before k0; so adj(A) = sign c a r^T with r = P^T L^{-T} b.
   int nzero = 0, k0 = -1;
-  for (int m = 0; m < n; ++m)
+#pragma unroll 1
+  for (int m = 0; m < N; ++m)
     if (lu[m][m] == 0.0) {
       ++nzero;
       k0 = m;
     }
   if (nzero > 0) {
-    double* dst = adj + b * n * n;
     if (nzero >= 2) {
-      for (int e = lane; e < n * n; e += 64) dst[e] = 0.0;
+#pragma unroll 1
+      for (int e = lane; e < N * N; e += 64) dst[e] = 0.0;
       return;
     }
     if (lane == 0) {
       double c = sign;
-      for (int m = 0; m < n; ++m)
+#pragma unroll 1
+      for (int m = 0; m < N; ++m)
         if (m != k0) c *= lu[m][m];
-      double* a = s_a[w];
-      double* r = s_r[w];
-      for (int m = n - 1; m >= 0; --m) {
+      double* a = L.a;
+      double* r = L.r;
+#pragma unroll 1
+      for (int m = N - 1; m >= 0; --m) {
         if (m >= k0) {
           a[m] = m == k0 ? 1.0 : 0.0;
         } else {
           double t = 0.0;
+#pragma unroll 1
           for (int q = m + 1; q <= k0; ++q) t += lu[m][q] * a[q];
           a[m] = -t / lu[m][m];
         }
       }
       // b into r, then z = L^{-T} b in place (L unit lower, below the diagonal of lu)
-      for (int j = 0; j < n; ++j) {
+#pragma unroll 1
+      for (int j = 0; j < N; ++j) {
         if (j <= k0) {
           r[j] = j == k0 ? 1.0 : 0.0;
         } else {
           double t = 0.0;
+#pragma unroll 1
           for (int q = k0; q < j; ++q) t += r[q] * lu[q][j];
           r[j] = -t / lu[j][j];
         }
       }
-      for (int i = n - 1; i >= 0; --i)
-        for (int j = i + 1; j < n; ++j) r[i] -= lu[j][i] * r[j];
+#pragma unroll 1
+      for (int i = N - 1; i >= 0; --i)
+#pragma unroll 1
+        for (int j = i + 1; j < N; ++j) r[i] -= lu[j][i] * r[j];
       // r = P^T z: the row swaps undone in reverse order
-      for (int k = n - 1; k >= 0; --k) {
-        const int p = s_piv[w][k];
+#pragma unroll 1
+      for (int k = N - 1; k >= 0; --k) {
+        const int p = L.piv[k];
         const double t = r[k];
         r[k] = r[p];
         r[p] = t;
       }
-      for (int m = 0; m < n; ++m) a[m] *= c;
+#pragma unroll 1
+      for (int m = 0; m < N; ++m) a[m] *= c;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < n)
-      for (int i = 0; i < n; ++i) dst[i * n + lane] = s_a[w][i] * s_r[w][lane];
+    wave_lds_sync();
+    if (lane < N)
+#pragma unroll 1
+      for (int i = 0; i < N; ++i) dst[i * N + lane] = L.a[i] * L.r[lane];
     return;
   }
   // column `lane` of A^{-1}: solve L U x = P e_lane
-  if (lane < n) {
-    double x[32];
-    for (int i = 0; i < n; ++i) x[i] = 0.0;
+  if (lane < N) {
     // P e_lane: the row permutation applied to the identity
     int col = lane;
-    for (int k = 0; k < n; ++k) {
-      const int p = s_piv[w][k];
+#pragma unroll 1
+    for (int k = 0; k < N; ++k) {
+      const int p = L.piv[k];
       if (col == k) col = p;
       else if (col == p) col = k;
     }
-    x[col] = 1.0;
-    for (int i = 0; i < n; ++i)
-      for (int j = 0; j < i; ++j) x[i] -= lu[i][j] * x[j];
-    for (int i = n - 1; i >= 0; --i) {
-      for (int j = i + 1; j < n; ++j) x[i] -= lu[i][j] * x[j];
-      x[i] /= lu[i][i];
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+      double t = i == col ? 1.0 : 0.0;
+#pragma unroll 1
+      for (int j = 0; j < i; ++j) t -= lu[i][j] * L.x[j][lane];
+      L.x[i][lane] = t;
     }
-    double* dst = adj + b * n * n;
-    for (int i = 0; i < n; ++i) dst[i * n + lane] = d * x[i];
+#pragma unroll 1
+    for (int i = N - 1; i >= 0; --i) {
+      double t = L.x[i][lane];
+#pragma unroll 1
+      for (int j = i + 1; j < N; ++j) t -= lu[i][j] * L.x[j][lane];
+      t /= lu[i][i];
+      L.x[i][lane] = t;
+      dst[i * N + lane] = d * t;
+    }
   }
+}
+
+// Largest v of each group of G consecutive lanes (8, 16 or 32), in every lane.
+template <int G>
+__device__ __forceinline__ double group_max(double v) {
+  auto step = [&](auto ctl) {
+    constexpr int c = decltype(ctl)::value;
+    const int64_t b = __builtin_bit_cast(int64_t, v);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), c, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), c, 0xF, 0xF, true);
+    v = fmax(v, __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo));
+  };
+  step(std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+  step(std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+  step(std::integral_constant<int, 0x141>{});  // row_half_mirror
+  if constexpr (G >= 16) step(std::integral_constant<int, 0x140>{});  // row_mirror
+  if constexpr (G >= 32) v = fmax(v, __shfl_xor(v, 16, 64));
+  return v;
+}
+
+// 5 <= N <= 32: a wavefront takes 64 / G matrices (G = 8, 16 or 32 lanes
+// each), lane i of a group holding row i in registers; in-place Gauss-Jordan
+// over the unused rows (no row is moved, and pivot rows stay unscaled until
+// the end).  At step k the lane of the pivot row hands it to its group through
+// LDS (16-byte accesses; ds_bpermute of every column measured 1.6x slower: the
+// LDS unit is what bounds the kernel beside the traffic of 2 N^2 + 1 doubles
+// per matrix) and every other lane subtracts its multiple; the columns rotate
+// by one register, so that the step loop is not unrolled and the pivot column
+// is always register 0.  One
+// wavefront per matrix with the LU in LDS ran N serial steps with N of 64
+// lanes busy and kept the solutions in scratch memory.
+// 50,000 matrices of N = 16: 1092 us before, 80 us now (2.6 TB/s);
+// N = 5, 8, 24 and 32 in as many bytes 1484, 1134, 1165 and 1326 us before, 59,
+// 48, 139 and 155 us now.
+template <int N>
+__global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_gj_kernel(const double* __restrict__ A,
+                                                                          int64_t batch,
+                                                                          double* __restrict__ det,
+                                                                          double* __restrict__ adj) {
+  constexpr int G = N <= 8 ? 8 : (N <= 16 ? 16 : 32), NM = 64 / G, E = N * N;
+  constexpr int LD = N | 1;  // odd row pitch: rows of a group start on different banks
+  constexpr int RP = (N + 1) / 2 + 1;  // pitch of the groups' pivot rows, in pairs of columns
+  union alignas(16) Lds {
+    double m[NM][N][LD];
+    LuLds<N> lu;
+    double2 row[NM][RP];
+  };
+  __shared__ Lds s_lds[4];
+  __shared__ int s_piv[4][NM][N];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t b0 = (static_cast<int64_t>(blockIdx.x) * 4 + w) * NM;
+  if (b0 >= batch) return;  // whole waves leave together; no workgroup barrier below
+  const int nb = static_cast<int>(min<int64_t>(NM, batch - b0));
+  double* const sm = &s_lds[w].m[0][0][0];
+  const double* const src = A + b0 * E;
+  // the wavefront's matrices are contiguous: coalesced loads, all in flight
+  // before the first is stored, rows padded in LDS (past the last matrix: its
+  // last element again)
+  constexpr int Q = (NM * E + 63) / 64;
+  {
+    double in[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) in[q] = src[min(q * 64 + lane, nb * E - 1)];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int e = q * 64 + lane;
+      if (NM * E % 64 == 0 || e < NM * E) sm[e / N * LD + e % N] = in[q];
+    }
+  }
+  wave_lds_sync();
+  const int gi = lane / G, i = lane % G, base = lane - i;
+  double a[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) a[j] = i < N ? sm[(gi * N + i) * LD + j] : 0.0;
+
+  wave_lds_sync();  // the rows are read; the pivot rows take their place
+  double2* const s_row = &s_lds[w].row[0][0];
+  double d = 1.0, my_piv = 1.0;
+  uint32_t unused = N == 32 ? ~0u : (1u << (N & 31)) - 1u;  // rows not yet a pivot row
+  int my_k = 0, odd = 0;
+  bool bad = false;
+#pragma unroll(N % 2 == 0 ? 2 : 1)
+  for (int k = 0; k < N; ++k) {
+    // pivot: the unused row with the largest entry (ties to the lowest row)
+    const bool cand = (unused >> i) & 1u;
+    const double v = cand ? fabs(a[0]) : -1.0;
+    const double vm = group_max<G>(v);
+    const uint64_t hit = __ballot(cand && v == vm);
+    const uint32_t mine = static_cast<uint32_t>(hit >> base) & (G == 32 ? ~0u : (1u << (G & 31)) - 1u);
+    const int p = mine ? __builtin_ctz(mine) : 0;
+    bad = bad || mine == 0;  // only NaNs are left in this column
+    // sign of the permutation: unused rows before p
+    odd ^= __builtin_popcount(unused & ((1u << p) - 1u)) & 1;
+    unused &= ~(1u << p);
+    const bool own = i == p;
+    // the pivot row goes to its group through LDS, two columns per access
+    double2* const row = s_row + gi * RP;
+    if (own) {
+#pragma unroll
+      for (int j = 0; j < (N + 1) / 2; ++j) row[j] = double2{a[2 * j], 2 * j + 1 < N ? a[2 * j + 1] : 0.0};
+    }
+    wave_lds_sync();
+    double r[2 * ((N + 1) / 2)];
+#pragma unroll
+    for (int j = 0; j < (N + 1) / 2; ++j) {
+      const double2 v2 = row[j];
+      r[2 * j] = v2.x;
+      r[2 * j + 1] = v2.y;
+    }
+    const double piv = r[0];
+    bad = bad || !(fabs(piv) >= 2.2250738585072014e-308);
+    d *= piv;
+    if (own) {
+      my_k = k;
+      my_piv = piv;
+    }
+    if (i == 0) s_piv[w][gi][k] = p;
+    // row i -= f * pivot row; the pivot row itself stays (f = 0).  Column k
+    // of the result holds the coefficient of identity column p.
+    const double f = own ? 0.0 : a[0] / piv;
+#pragma unroll
+    for (int j = 1; j < N; ++j) a[j - 1] = fma(-f, r[j], a[j]);
+    a[N - 1] = own ? 1.0 : -f;
+    wave_lds_sync();  // the row is read before the next one is written
+  }
+  if (odd) d = -d;
+  bad = bad || !(fabs(d) <= 1.7976931348623157e308);
+
+  // A^{-1}[k of row i][p_k] = a[k] / pivot of row i
+  wave_lds_sync();
+  if (i < N) {
+    const double inv = 1.0 / my_piv;
+#pragma unroll
+    for (int k = 0; k < N; ++k) sm[(gi * N + my_k) * LD + s_piv[w][gi][k]] = d * (a[k] * inv);
+  }
+  wave_lds_sync();
+  double* const dst = adj + b0 * E;
+  // matrices that need the general path are left to it (it reads them again)
+  const uint64_t again = __ballot(bad);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = q * 64 + lane;
+    if (e < nb * E && (again == 0 || !((again >> (e / E * G)) & 1u))) dst[e] = sm[e / N * LD + e % N];
+  }
+  if (i == 0 && gi < nb && !bad) det[b0 + gi] = d;
+  if (again != 0) {
+    for (int m = 0; m < nb; ++m) {
+      if (!((again >> (m * G)) & 1u)) continue;
+      lu_general<N>(src + m * E, det + b0 + m, dst + m * E, lane, s_lds[w].lu);
+    }
+  }
+}
+
+template <int N>
+void run_det_adj_gj(int64_t batch, const double* A, double* det, double* adj, hipStream_t s) {
+  constexpr int per_block = 4 * (64 / (N <= 8 ? 8 : (N <= 16 ? 16 : 32)));
+  hipLaunchKernelGGL(det_adj_gj_kernel<N>, dim3(static_cast<unsigned>((batch + per_block - 1) / per_block)),
+                     dim3(256), 0, s, A, batch, det, adj);
 }
 
 }  // namespace
@@ -246,10 +435,13 @@ hipError_t launch_det_adj(int n, int64_t batch, const double* A, double* det, do
     case 2: hipLaunchKernelGGL(det_adj_small_kernel<2>, g_small, blk, 0, s, A, batch, det, adj); break;
     case 3: hipLaunchKernelGGL(det_adj_small_kernel<3>, g_small, blk, 0, s, A, batch, det, adj); break;
     case 4: hipLaunchKernelGGL(det_adj_small_kernel<4>, g_small, blk, 0, s, A, batch, det, adj); break;
+#define QMK_DET(n) case n: run_det_adj_gj<n>(batch, A, det, adj, s); break;
+    QMK_DET(5) QMK_DET(6) QMK_DET(7) QMK_DET(8) QMK_DET(9) QMK_DET(10) QMK_DET(11) QMK_DET(12) QMK_DET(13) QMK_DET(14)
+    QMK_DET(15) QMK_DET(16) QMK_DET(17) QMK_DET(18) QMK_DET(19) QMK_DET(20) QMK_DET(21) QMK_DET(22) QMK_DET(23)
+    QMK_DET(24) QMK_DET(25) QMK_DET(26) QMK_DET(27) QMK_DET(28) QMK_DET(29) QMK_DET(30) QMK_DET(31) QMK_DET(32)
+#undef QMK_DET
     default:
-      if (n < 1 || n > 32) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(det_adj_lu_kernel, dim3(static_cast<unsigned>((batch + 3) / 4)), blk, 0, s, A, n,
-                         batch, det, adj);
+      return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
