@@ -130,6 +130,15 @@ qmk_status qmk_set_basis(qmk_ctx ctx, int64_t shell_num, int64_t prim_num,
  * (Section 3.2).  ao_num must match the basis.  Invalidates cached MOs. */
 qmk_status qmk_set_mo_coef(qmk_ctx ctx, int64_t mo_num, int64_t ao_num, const double* coef);
 
+/* qmk_set_nucleus and qmk_set_mo_coef in one call for parameters that a
+ * program holds on the GPU (an optimiser's; Section 2.2, inputs of a context):
+ * coord[nucl_num][3] and coef[mo_num][ao_num] are DEVICE arrays, copied on
+ * hip_stream; the call waits for that stream.  Requires the basis.  The same
+ * values are accepted and refused; on an error the context keeps the nuclei
+ * and coefficients that it had. */
+qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* coord, int64_t mo_num,
+                                 int64_t ao_num, const double* coef, void* hip_stream);
+
 /* Electron / grid coordinates for walk_num walkers of elec_num electrons
  * (Section 5.1, set_point).  transp = 'N': coord[walk][elec][3];
  * transp = 'T': coord[3][walk*elec].  coord_on_device = 0: host memory,

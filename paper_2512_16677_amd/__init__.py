@@ -18,6 +18,7 @@ Typical use (mirrors the call sequence of the QMCkl paper, Section 5.1)::
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Dict, Optional
 
@@ -44,7 +45,7 @@ QMK_F64, QMK_F32 = 0, 1
 
 EXPORTED = [
     "qmk_status_string", "qmk_last_error", "qmk_ctx_create", "qmk_ctx_destroy",
-    "qmk_set_precision", "qmk_set_nucleus", "qmk_set_basis", "qmk_set_mo_coef",
+    "qmk_set_precision", "qmk_set_nucleus", "qmk_set_basis", "qmk_set_mo_coef", "qmk_set_params_device",
     "qmk_set_point", "qmk_get_dims", "qmk_get_ao_vgl", "qmk_get_mo_vgl", "qmk_get_mo_vgl_noalloc",
     "qmk_get_mo_value", "qmk_get_density", "qmk_set_mo_cusp", "qmk_set_screening",
     "qmk_get_screening_density", "qmk_det_adj", "qmk_jastrow_een_terms", "qmk_jastrow_een",
@@ -86,6 +87,7 @@ def load_library(path: str = LIB_PATH):
         "qmk_set_nucleus": ([P, I64, P], I32),
         "qmk_set_basis": ([P, I64, I64, P, P, P, P, P, P, P, P], I32),
         "qmk_set_mo_coef": ([P, I64, I64, P], I32),
+        "qmk_set_params_device": ([P, I64, P, I64, I64, P, P], I32),
         "qmk_set_point": ([P, ctypes.c_char, I64, I64, P, I32], I32),
         "qmk_get_dims": ([P, P, P, P, P, P], I32),
         "qmk_get_ao_vgl": ([P, P, I64, I32, P], I32),
@@ -233,6 +235,16 @@ class Context:
             raise ValueError("coef must have shape [mo_num, ao_num]")
         self._in_version += 1
         self._check(self._lib.qmk_set_mo_coef(self._h, c.shape[0], c.shape[1], _ptr(c)))
+
+    def _set_params_device(self, coord, coef):
+        """set_nucleus and set_mo_coef from contiguous CUDA float64 tensors of
+        this context's device, without a copy through the host."""
+        if coef.dim() != 2:
+            raise ValueError("coef must have shape [mo_num, ao_num]")
+        r = coord.reshape(-1, 3)
+        self._in_version += 1
+        self._check(self._lib.qmk_set_params_device(self._h, r.shape[0], _ptr(r), coef.shape[0], coef.shape[1],
+                                                    _ptr(coef), _stream()))
 
     def set_point(self, coord, walk_num: Optional[int] = None, elec_num: Optional[int] = None,
                   transp: str = "N"):
@@ -557,19 +569,28 @@ class Batch:
             pass
 
 
+@functools.lru_cache(maxsize=None)
 def _autograd():
     import torch
+
+    def set_params(qctx, nucl, coef):
+        if isinstance(coef, torch.Tensor):
+            qctx._set_params_device(nucl, coef)
+        else:
+            qctx.set_nucleus(nucl)
+            qctx.set_mo_coef(coef)
 
     class MoVgl(torch.autograd.Function):
         """mo_vgl(C, R_nucl, R_elec) with a hand-written adjoint.
 
         forward(ctx, qctx, C [mo,ao], R_nucl [nucl,3], R_elec [walk,elec,3])
-        -> [walk, elec, 5, mo].  C and R_nucl are copied to the context (host
-        round trip, small arrays); R_elec stays on the device.  backward
+        -> [walk, elec, 5, mo].  C and R_nucl are copied to the context (on
+        the device when they are there, else through the host); R_elec stays
+        on the device.  backward
         calls the library's adjoint, which recomputes AO derivatives up to
         third order instead of storing them.
 
-        One context may serve several graphs: forward keeps host copies of C
+        One context may serve several graphs: forward keeps copies of C
         and R_nucl and the device coordinates, and backward puts them back
         into the context when another forward (or any set_* call of the
         inputs) ran in between, so every graph gets the gradients of its own
@@ -578,16 +599,19 @@ def _autograd():
 
         @staticmethod
         def forward(ctx, qctx: Context, C, R_nucl, R_elec):
-            nucl = R_nucl.detach().double().cpu().numpy().copy()
-            coef = C.detach().double().cpu().numpy().copy()
-            qctx.set_nucleus(nucl)
-            qctx.set_mo_coef(coef)
+            if all(t.is_cuda and t.device.index == qctx.device for t in (C, R_nucl)):
+                nucl, coef = (t.detach().to(torch.float64, copy=True, memory_format=torch.contiguous_format)
+                              for t in (R_nucl, C))
+            else:
+                nucl = R_nucl.detach().double().cpu().numpy().copy()
+                coef = C.detach().double().cpu().numpy().copy()
+            set_params(qctx, nucl, coef)
             r = R_elec.detach().to(torch.float64).contiguous()
             qctx.set_point(r)
             mo = qctx.get_mo_vgl()
             ctx.qctx = qctx
             ctx.devices = (C.device, R_nucl.device, R_elec.device)
-            ctx.host_inputs = (nucl, coef)
+            ctx.params = (nucl, coef)
             ctx.versions = (qctx._in_version, qctx._cfg_version)
             ctx.save_for_backward(r)
             return mo
@@ -601,9 +625,7 @@ def _autograd():
                                    "between forward and backward")
             if qctx._in_version != in_v:
                 (r,) = ctx.saved_tensors
-                nucl, coef = ctx.host_inputs
-                qctx.set_nucleus(nucl)
-                qctx.set_mo_coef(coef)
+                set_params(qctx, *ctx.params)
                 qctx.set_point(r)
                 ctx.versions = (qctx._in_version, qctx._cfg_version)
             g = qctx.adjoint(grad.contiguous(), d_coef=ctx.needs_input_grad[1],

@@ -509,7 +509,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
     if (c->cusp_on)
       return bfail(b, QMK_UNSUPPORTED, "context " + std::to_string(i) + " has the cusp correction on");
     if ((st = ensure_tables(c)) != QMK_OK) return bfail(b, st, c->err);
-    if ((st = ensure_coef(c)) != QMK_OK) return bfail(b, st, c->err);
+    if ((st = ensure_coef(c, s)) != QMK_OK) return bfail(b, st, c->err);
     key.insert(key.end(), {c->P(), c->ao_num, c->mo_num, c->nucl_num, c->n_groups, c->nucl_dev,
                            static_cast<int64_t>(c->tab.smem_bytes)});
   }

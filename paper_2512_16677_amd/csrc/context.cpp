@@ -252,75 +252,47 @@ qmk_status ensure_tables(qmk_ctx ctx) {
   return QMK_OK;
 }
 
-// Round-to-nearest-even FP32 -> BF16 (bit pattern) and back.
-uint16_t bf16_bits(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
-}
-float bf16_value(uint16_t h) {
-  const uint32_t u = static_cast<uint32_t>(h) << 16;
-  float f;
-  std::memcpy(&f, &u, 4);
-  return f;
-}
-
-qmk_status ensure_coef(qmk_ctx ctx) {
+// The products' copies of C for the current mode, made by one kernel from the
+// FP64 coefficients on the device.  Waits for them, so that every stream
+// may read them afterwards (as after the upload).
+qmk_status make_coef_copies(qmk_ctx ctx, const double* src, hipStream_t s) {
   const int want = ctx->mode == QMK_FP64 ? 0 : (ctx->mode == QMK_MIXED_F32 ? 1 : 2);
-  if (!ctx->coef_dirty && ctx->coef_mode == want) return QMK_OK;
-  if (want == 2) {
-    // C split once into bf16 hi + lo (hi = bf16(c), lo = bf16(c - hi)), in
-    // the two layouts the products read: [n][k] and [k][n].
-    const int64_t K = ctx->ao_num, N = ctx->mo_num;
-    ctx->Kp = round_up(K, kAoPad);
-    ctx->Np = round_up(N, kMoPad);
-    const int64_t Kp = ctx->Kp, Np = ctx->Np;
-    std::vector<uint16_t> ch(Kp * Np, 0), cl(Kp * Np, 0), th(Kp * Np, 0), tl(Kp * Np, 0);
-    for (int64_t n = 0; n < N; ++n)
-      for (int64_t k = 0; k < K; ++k) {
-        const double v = ctx->C[n * K + k];
-        const uint16_t h = bf16_bits(static_cast<float>(v));
-        const uint16_t l = bf16_bits(static_cast<float>(v - static_cast<double>(bf16_value(h))));
-        ch[n * Kp + k] = h;
-        cl[n * Kp + k] = l;
-        th[k * Np + n] = h;
-        tl[k * Np + n] = l;
-      }
-    const size_t bytes = static_cast<size_t>(Kp * Np) * 2;
-    DevBuf* bufs[4] = {&ctx->d_Cb_hi, &ctx->d_Cb_lo, &ctx->d_Ctb_hi, &ctx->d_Ctb_lo};
-    const std::vector<uint16_t>* src[4] = {&ch, &cl, &th, &tl};
-    for (int i = 0; i < 4; ++i) {
-      QMK_HIP(ctx, bufs[i]->ensure(bytes), "alloc split C");
-      QMK_HIP(ctx, hipMemcpy(bufs[i]->p, src[i]->data(), bytes, hipMemcpyHostToDevice), "upload split C");
-    }
-    // the FP32 copies below serve the value-only products, which have no
-    // BF16x3 form
-  }
   const int64_t K = ctx->ao_num, N = ctx->mo_num;
   ctx->Kp = round_up(K, kAoPad);
   ctx->Np = round_up(N, kMoPad);
-  const int64_t Kp = ctx->Kp, Np = ctx->Np;
-  const size_t esz = want ? sizeof(float) : sizeof(double);
-  std::vector<unsigned char> ct(static_cast<size_t>(Kp * Np) * esz, 0), cn(ct.size(), 0);
-  for (int64_t n = 0; n < N; ++n)
-    for (int64_t k = 0; k < K; ++k) {
-      const double v = ctx->C[n * K + k];
-      if (want) {
-        reinterpret_cast<float*>(ct.data())[k * Np + n] = static_cast<float>(v);
-        reinterpret_cast<float*>(cn.data())[n * Kp + k] = static_cast<float>(v);
-      } else {
-        reinterpret_cast<double*>(ct.data())[k * Np + n] = v;
-        reinterpret_cast<double*>(cn.data())[n * Kp + k] = v;
-      }
-    }
-  QMK_HIP(ctx, ctx->d_Ct.ensure(ct.size()), "alloc C^T");
-  QMK_HIP(ctx, hipMemcpy(ctx->d_Ct.p, ct.data(), ct.size(), hipMemcpyHostToDevice), "upload C^T");
-  QMK_HIP(ctx, ctx->d_C.ensure(cn.size()), "alloc C");
-  QMK_HIP(ctx, hipMemcpy(ctx->d_C.p, cn.data(), cn.size(), hipMemcpyHostToDevice), "upload C");
+  const size_t n = static_cast<size_t>(ctx->Kp * ctx->Np);
+  // (in the BF16x3 mode the FP32 copies serve the value-only products)
+  QMK_HIP(ctx, ctx->d_Ct.ensure(n * (want ? 4 : 8)), "alloc C^T");
+  QMK_HIP(ctx, ctx->d_C.ensure(n * (want ? 4 : 8)), "alloc C");
+  if (want == 2)
+    for (DevBuf* b : {&ctx->d_Cb_hi, &ctx->d_Cb_lo, &ctx->d_Ctb_hi, &ctx->d_Ctb_lo})
+      QMK_HIP(ctx, b->ensure(n * 2), "alloc split C");
+  const CoefCopies o{ctx->d_C.p, ctx->d_Ct.p, ctx->d_Cb_hi.p, ctx->d_Cb_lo.p, ctx->d_Ctb_hi.p, ctx->d_Ctb_lo.p};
+  QMK_HIP(ctx, launch_coef_layout(src, N, K, ctx->Np, ctx->Kp, want, o, s), "lay out C");
+  QMK_HIP(ctx, hipStreamSynchronize(s), "lay out C");
   ctx->coef_dirty = false;
   ctx->coef_mode = want;
+  return QMK_OK;
+}
+
+qmk_status ensure_coef(qmk_ctx ctx, hipStream_t s) {
+  const int want = ctx->mode == QMK_FP64 ? 0 : (ctx->mode == QMK_MIXED_F32 ? 1 : 2);
+  if (!ctx->coef_dirty && ctx->coef_mode == want) return QMK_OK;
+  if (!ctx->craw_valid) {
+    QMK_HIP(ctx, ctx->d_Craw.ensure(ctx->C.size() * 8), "alloc C");
+    QMK_HIP(ctx, hipMemcpy(ctx->d_Craw.p, ctx->C.data(), ctx->C.size() * 8, hipMemcpyHostToDevice), "upload C");
+    ctx->craw_valid = true;
+  }
+  ctx->coef_dirty = true;  // the copies are neither mode's until all of them are made
+  return make_coef_copies(ctx, ctx->d_Craw.as<double>(), s);
+}
+
+// Host copy of the coefficients, fetched if only the device holds them.
+qmk_status host_coef(qmk_ctx ctx) {
+  if (!ctx->C.empty()) return QMK_OK;
+  std::vector<double> c(static_cast<size_t>(ctx->mo_num * ctx->coef_ao));
+  QMK_HIP(ctx, hipMemcpy(c.data(), ctx->d_Craw.p, c.size() * 8, hipMemcpyDeviceToHost), "download C");
+  ctx->C = std::move(c);
   return QMK_OK;
 }
 
@@ -344,7 +316,7 @@ qmk_status check_ready(qmk_ctx ctx, bool need_coef) {
   if (!ctx->has_points) return fail(ctx, QMK_NOT_SET, "points not set");
   if (need_coef) {
     if (!ctx->has_coef) return fail(ctx, QMK_NOT_SET, "MO coefficients not set");
-    if (ctx->C.size() != static_cast<size_t>(ctx->mo_num * ctx->ao_num))
+    if (ctx->coef_ao != ctx->ao_num)
       return fail(ctx, QMK_NOT_SET, "MO coefficients do not match the basis (ao_num changed)");
   }
   return QMK_OK;
@@ -521,7 +493,7 @@ qmk_status ensure_cusp(qmk_ctx ctx, hipStream_t s) {
   const int64_t key[4] = {ctx->geom_version, ctx->coef_version, ctx->cusp_version, ctx->mode};
   if (std::equal(key, key + 4, ctx->cusp_key)) return QMK_OK;
   qmk_status st = ensure_tables(ctx);
-  if (st != QMK_OK) return st;
+  if (st != QMK_OK || (st = host_coef(ctx)) != QMK_OK) return st;
   const int64_t nn = ctx->nucl_num, K = ctx->ao_num, N = ctx->mo_num;
   const double* R = ctx->nucl.data();
   for (int64_t a = 0; a < nn; ++a)
@@ -980,9 +952,76 @@ qmk_status qmk_set_mo_coef(qmk_ctx ctx, int64_t mo_num, int64_t ao_num, const do
   for (int64_t i = 0; i < mo_num * ao_num; ++i)
     if (!std::isfinite(coef[i])) return fail(ctx, QMK_NONFINITE, "non-finite MO coefficient");
   ctx->C.assign(coef, coef + mo_num * ao_num);
+  ctx->craw_valid = false;
+  ctx->coef_ao = ao_num;
   ctx->mo_num = mo_num;
   ctx->has_coef = true;
   ctx->coef_dirty = true;
+  ++ctx->coef_version;
+  return QMK_OK;
+}
+
+qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* coord, int64_t mo_num,
+                                 int64_t ao_num, const double* coef, void* hip_stream) {
+  QMK_CHECK_CTX(ctx);
+  if (nucl_num < 1 || nucl_num > (1 << 24)) return bad_arg(ctx, 2, "nucl_num must be >= 1");
+  if (!ctx->has_basis) return fail(ctx, QMK_NOT_SET, "set the basis before the MO coefficients");
+  if (nucl_num != ctx->nucl_num) return bad_arg(ctx, 2, "number of nuclei changed while a basis is set");
+  if (mo_num < 1 || mo_num > (1 << 24)) return bad_arg(ctx, 4, "mo_num must be >= 1");
+  if (ao_num != ctx->ao_num) return bad_arg(ctx, 5, "ao_num does not match the basis");
+  DeviceGuard g(ctx->device);
+  qmk_status st;
+  if ((st = check_dev_arg(ctx, 3, coord)) != QMK_OK || (st = check_dev_arg(ctx, 6, coef)) != QMK_OK) return st;
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  const int64_t n = mo_num * ao_num, n3 = 3 * nucl_num;
+  const size_t pin_need = 16 + static_cast<size_t>(n3) * 8;
+  if (ctx->pin_bytes < pin_need) {
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
+    ctx->pin = nullptr;
+    ctx->pin_bytes = 0;
+    QMK_HIP(ctx, hipHostMalloc(&ctx->pin, pin_need, hipHostMallocDefault), "alloc pinned parameters");
+    ctx->pin_bytes = pin_need;
+  }
+  QMK_HIP(ctx, ctx->d_Craw_new.ensure(static_cast<size_t>(n) * 8), "alloc C");
+  int32_t* const flag = static_cast<int32_t*>(ctx->pin);
+  double* const host_xyz = reinterpret_cast<double*>(static_cast<char*>(ctx->pin) + 16);
+  *flag = 0;
+  // the tables keep their shape when the nuclei move: their centres are
+  // written in place, unless the tables are to be built anyway
+  const bool move = !ctx->tables_dirty;
+  if (move) ctx->tables_dirty = true;  // until the new centres are accepted
+  QMK_HIP(ctx, launch_take_params(coef, ctx->d_Craw_new.as<double>(), n, coord, nucl_num, host_xyz,
+                                  move ? ctx->d_nuc.as<NucDev>() : nullptr, move ? ctx->nucl_dev : 0, flag, s),
+          "take parameters");
+  // the products' copies of C are made before they are known to be finite, so
+  // that there is one wait; refused ones are laid out again from the kept C
+  const int64_t mo_before = ctx->mo_num;
+  ctx->mo_num = mo_num;
+  ctx->coef_dirty = true;
+  st = make_coef_copies(ctx, ctx->d_Craw_new.as<double>(), s);
+  if (st != QMK_OK) {
+    ctx->mo_num = mo_before;
+    ctx->coef_dirty = true;
+    return st;
+  }
+  for (int64_t i = 0; st == QMK_OK && i < n3; ++i)
+    if (!std::isfinite(host_xyz[i])) st = fail(ctx, QMK_NONFINITE, "non-finite nuclear coordinate");
+  if (st == QMK_OK && *flag) st = fail(ctx, QMK_NONFINITE, "non-finite MO coefficient");
+  if (st != QMK_OK) {
+    ctx->mo_num = mo_before;
+    ctx->coef_dirty = true;
+    return st;
+  }
+  ctx->nucl.assign(host_xyz, host_xyz + n3);
+  if (move) ctx->tables_dirty = false;
+  std::swap(ctx->d_Craw.p, ctx->d_Craw_new.p);
+  std::swap(ctx->d_Craw.bytes, ctx->d_Craw_new.bytes);
+  ctx->craw_valid = true;
+  ctx->C.clear();
+  ctx->coef_ao = ao_num;
+  ctx->has_coef = true;
+  ++ctx->date;
+  ++ctx->geom_version;
   ++ctx->coef_version;
   return QMK_OK;
 }
@@ -1345,7 +1384,7 @@ qmk_status qmk_get_mo_vgl(qmk_ctx ctx, void* out, int64_t size_max, int32_t dtyp
     return fail(ctx, QMK_SIZE, "size_max " + std::to_string(size_max) + " < " + std::to_string(P * 5 * N));
   DeviceGuard g(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if ((st = ensure_coef(ctx)) != QMK_OK) return st;
+  if ((st = ensure_coef(ctx, s)) != QMK_OK) return st;
   if (ctx->sparse) {
     if ((st = get_mo_vgl_screened(ctx, out, dtype, s)) != QMK_OK) return st;
     return apply_cusp(ctx, out, dtype == QMK_F32, s);
@@ -1413,7 +1452,7 @@ qmk_status qmk_get_mo_value(qmk_ctx ctx, void* out, int64_t size_max, int32_t dt
   DeviceGuard g(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const Prec prec = ctx->mode == QMK_FP64 ? Prec::kF64 : Prec::kF32;
-  if ((st = ensure_coef(ctx)) != QMK_OK) return st;
+  if ((st = ensure_coef(ctx, s)) != QMK_OK) return st;
   const void* plane = nullptr;
   int64_t row = 0;
   if ((st = provide_ao_value(ctx, s, &plane, &row)) != QMK_OK) return st;
@@ -1472,6 +1511,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
   // occupied MOs, compacted once per (occupations, coefficients, precision)
   std::vector<double> key(occ, occ + N);
   if (key != ctx->occ_key || ctx->occ_coef_version != ctx->coef_version || ctx->occ_f32 != f32) {
+    if ((st = host_coef(ctx)) != QMK_OK) return st;
     std::vector<int64_t> rows;
     for (int64_t n = 0; n < N; ++n)
       if (occ[n] != 0.0) rows.push_back(n);
@@ -1574,7 +1614,7 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
   if (ctx->cusp_on) return fail(ctx, QMK_UNSUPPORTED, "the adjoint with the cusp correction on is not implemented");
   DeviceGuard g(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if ((st = ensure_coef(ctx)) != QMK_OK) return st;
+  if ((st = ensure_coef(ctx, s)) != QMK_OK) return st;
   // screened adjoint: every product in sorted point order (Section 3.2)
   const bool scr = ctx->sparse;
   // dC reads the AO values: by default the forward pass's array of the same

@@ -8,6 +8,12 @@
 // multiple of four weights, so that both products can load it in 16-byte
 // pieces; the same padded copy (without conversion) serves weights whose row
 // length does not allow that.
+//
+// The copies of the MO coefficients that the products read (both layouts,
+// padded, in the mode's types) are made here too.
+#include <algorithm>
+#include <type_traits>
+
 #include "qmk_internal.h"
 
 namespace qmk {
@@ -123,7 +129,94 @@ __global__ __launch_bounds__(256) void split_w_batch_kernel(const SplitJob* __re
            static_cast<__bf16*>(j.hi), static_cast<__bf16*>(j.lo), static_cast<uint32_t>(e - prefix[jb]));
 }
 
+// The products' copies of C [N][K] (FP64): C [Np][Kp] and C^T [Kp][Np] in FP64
+// (MODE 0) or FP32 (1, 2), and in MODE 2 both split into bf16 hi / lo planes
+// (hi = bf16(c), lo = bf16(c - hi), the residual in FP64); zeros beyond N
+// and K.  Np and Kp are multiples of 32.  One 32 x 32 tile per workgroup,
+// transposed through LDS, so that every copy is stored in full lines.  Bound
+// by the latency of one pass: 800 AOs x 400 MOs 7 us, where the host loops and
+// 4 to 6 blocking uploads that this replaces took 3 ms.
+template <int MODE>
+__global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restrict__ src, int64_t N, int64_t K,
+                                                          int64_t Np, int64_t Kp, CoefCopies o) {
+  typedef typename std::conditional<MODE == 0, double, float>::type T;
+  __shared__ double tile[32][33];
+  const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 32, n0 = static_cast<int64_t>(blockIdx.y) * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  auto put = [](const CoefCopies& c, bool transposed, int64_t at, double v) {
+    static_cast<T*>(transposed ? c.ct : c.c)[at] = static_cast<T>(v);
+    if constexpr (MODE == 2) {
+      float f = static_cast<float>(v);
+      // hi is the bf16 rounding of the FP32 value (not one FP64 -> bf16 rounding)
+      asm volatile("" : "+v"(f));
+      const __bf16 h = static_cast<__bf16>(f);
+      float r = static_cast<float>(v - static_cast<double>(static_cast<float>(h)));
+      asm volatile("" : "+v"(r));
+      static_cast<__bf16*>(transposed ? c.ct_hi : c.c_hi)[at] = h;
+      static_cast<__bf16*>(transposed ? c.ct_lo : c.c_lo)[at] = static_cast<__bf16>(r);
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t n = n0 + ty + 8 * q, k = k0 + tx;
+    const double v = n < N && k < K ? src[n * K + k] : 0.0;
+    put(o, false, n * Kp + k, v);
+    tile[ty + 8 * q][tx] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) put(o, true, (k0 + ty + 8 * q) * Np + n0 + tx, tile[tx][ty + 8 * q]);
+}
+
+// dst = src, with *flag = 1 where a value is not finite; the first workgroup
+// also copies the nuclei to `nucl_out` (host memory) and, where `nuc` is
+// given, into the nucleus table.
+__global__ __launch_bounds__(256) void take_params_kernel(const double* __restrict__ src, double* __restrict__ dst,
+                                                          int64_t n, const double* __restrict__ nucl, int64_t n_nucl,
+                                                          double* __restrict__ nucl_out, NucDev* __restrict__ nuc,
+                                                          int32_t n_nuc, int32_t* __restrict__ flag) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  bool bad = false;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const double v = src[i];
+    dst[i] = v;
+    bad = bad || !isfinite(v);
+  }
+  if (bad) *flag = 1;
+  if (blockIdx.x != 0) return;
+  for (int64_t i = threadIdx.x; i < 3 * n_nucl; i += blockDim.x) nucl_out[i] = nucl[i];
+  if (nuc)
+    for (int32_t a = threadIdx.x; a < n_nuc; a += blockDim.x) {
+      const double* r = nucl + 3 * static_cast<int64_t>(nuc[a].orig);
+      nuc[a].x = r[0];
+      nuc[a].y = r[1];
+      nuc[a].z = r[2];
+    }
+}
+
 }  // namespace
+
+hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
+                              const CoefCopies& o, hipStream_t s) {
+  if (N <= 0 || K <= 0) return hipSuccess;
+  if (Np % 32 != 0 || Kp % 32 != 0 || Np < N || Kp < K || Np / 32 > 65535) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(Kp / 32), static_cast<unsigned>(Np / 32));
+  if (mode == 0)
+    hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+  else if (mode == 1)
+    hipLaunchKernelGGL(coef_layout_kernel<1>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+  else
+    hipLaunchKernelGGL(coef_layout_kernel<2>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+  return hipGetLastError();
+}
+
+hipError_t launch_take_params(const double* coef, double* coef_out, int64_t n, const double* nucl, int64_t n_nucl,
+                              double* nucl_out, NucDev* nuc, int32_t n_nuc, int32_t* flag, hipStream_t s) {
+  const int64_t blocks = std::min<int64_t>((n + 255) / 256, 1024);
+  hipLaunchKernelGGL(take_params_kernel, dim3(static_cast<unsigned>(std::max<int64_t>(blocks, 1))), dim3(256), 0, s,
+                     coef, coef_out, n, nucl, n_nucl, nucl_out, nuc, n_nuc, flag);
+  return hipGetLastError();
+}
 
 hipError_t launch_split_w(const void* w, int w_is_f32, int64_t P, int64_t N, int64_t Pp, int64_t Nw,
                           const int32_t* perm, void* hi, void* lo, hipStream_t s) {

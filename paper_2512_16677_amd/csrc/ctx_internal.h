@@ -80,7 +80,8 @@ struct qmk_ctx_s {
 
   bool has_coef = false;
   int64_t mo_num = 0;
-  std::vector<double> C;  // [mo][ao]
+  std::vector<double> C;  // [mo][ao]; empty while only the device holds them (host_coef)
+  int64_t coef_ao = 0;    // AOs that the coefficients were set for
 
   bool has_points = false;
   int64_t walk_num = 0, elec_num = 0;
@@ -98,6 +99,11 @@ struct qmk_ctx_s {
   bool coef_dirty = true;
   int coef_mode = -1;
   int64_t Kp = 0, Np = 0;
+  DevBuf d_Craw;             // C [mo][ao] in FP64
+  bool craw_valid = false;   // d_Craw holds the current coefficients
+  DevBuf d_Craw_new;         // qmk_set_params_device: candidates until they are checked
+  void* pin = nullptr;       // pinned host memory that a kernel writes: flag, nuclei
+  size_t pin_bytes = 0;
   DevBuf d_Ct, d_C;          // FP64 or FP32 copies: C^T [Kp][Np], C [Np][Kp]
   DevBuf d_Cb_hi, d_Cb_lo;   // BF16x3: C [Np][Kp] split into bf16 hi / lo
   DevBuf d_Ctb_hi, d_Ctb_lo; // BF16x3: C^T [Kp][Np] split
@@ -173,6 +179,7 @@ struct qmk_ctx_s {
       (void)hipEventDestroy(p.b);
     }
     for (auto e : event_pool) (void)hipEventDestroy(e);
+    if (pin) (void)hipHostFree(pin);
   }
 
   int64_t P() const { return walk_num * elec_num; }
@@ -202,7 +209,8 @@ qmk_status check_dev_arg(qmk_ctx ctx, int k, const void* p);
 qmk_status hip_fail(qmk_ctx ctx, hipError_t e, const char* what);
 bool valid_ctx(qmk_ctx ctx);
 qmk_status ensure_tables(qmk_ctx ctx);
-qmk_status ensure_coef(qmk_ctx ctx);
+// s: the stream that the copies are made on (complete on return).
+qmk_status ensure_coef(qmk_ctx ctx, hipStream_t s);
 qmk_status check_ready(qmk_ctx ctx, bool need_coef);
 PointArgs point_args(qmk_ctx ctx);
 Prec gemm_prec(qmk_ctx ctx);

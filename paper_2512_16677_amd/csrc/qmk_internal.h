@@ -322,6 +322,21 @@ int gemm_bf16p_blocks_per_cu(GemmKind kind, int cfg, int out_is_f32);
 hipError_t launch_split_w(const void* w, int w_is_f32, int64_t P, int64_t N, int64_t Pp, int64_t Nw,
                           const int32_t* perm, void* hi, void* lo, hipStream_t s);
 
+// The products' copies of the MO coefficients (see coef_layout_kernel): c / ct
+// FP64 or FP32, the planes in the BF16x3 mode only.
+struct CoefCopies {
+  void *c, *ct;
+  void *c_hi, *c_lo, *ct_hi, *ct_lo;
+};
+// mode: 0 FP64, 1 FP32, 2 FP32 and bf16 planes.
+hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
+                              const CoefCopies& o, hipStream_t s);
+// n coefficients to coef_out, with *flag = 1 (device-visible, cleared by the
+// caller) if one is not finite; n_nucl nuclei to nucl_out and, unless nuc is
+// NULL, into the n_nuc entries of the nucleus table.
+hipError_t launch_take_params(const double* coef, double* coef_out, int64_t n, const double* nucl, int64_t n_nucl,
+                              double* nucl_out, NucDev* nuc, int32_t n_nuc, int32_t* flag, hipStream_t s);
+
 // Autotuner (tuner.cpp).
 struct GemmProblem {
   GemmKind kind;
