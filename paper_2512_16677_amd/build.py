@@ -20,14 +20,14 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Per-unit code generation flags.  The FP32 products (units 4-6, whose FP32
-# accumulators are converted to FP64 on output), the density and Jastrow
-# products (units 7 and 10, whose epilogues do arithmetic on the
-# accumulators) and the BF16x3 units accumulate in vector registers, so that
+# accumulators are converted to FP64 on output), the density products (unit 7)
+# and the Jastrow product, whose epilogues do arithmetic on the accumulators,
+# and the BF16x3 units accumulate in vector registers, so that
 # the accumulators are not copied between register files on every K step (and
 # the large tiles do not spill).  The FP64 units store the accumulation
 # registers directly and are faster without it.
 VGPR_ACC = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-UNIT_FLAGS = {u: VGPR_ACC for u in (4, 5, 6, 7, 10)}
+UNIT_FLAGS = {u: VGPR_ACC for u in (4, 5, 6, 7)}
 
 # (source, extra defines, object name): the MFMA product sources are compiled
 # once per (precision, product) unit so that their many tile instantiations
@@ -37,9 +37,10 @@ SOURCES = [("context.cpp", [], None), ("batch.cpp", [], None), ("tuner.cpp", [],
            ("cusp_kernels.hip", [], None), ("sort_kernels.hip", [], None),
            ("det_kernels.hip", [], None), ("jastrow_kernels.hip", [], None), ("convert_kernels.hip", [], None),
            ("noalloc.hip", [], None),
+           ("jastrow_product.hip", VGPR_ACC, None),
            ("gemm_kernels.hip", [], None)]
 SOURCES += [("gemm_kernels.hip", [f"-DQMK_GEMM_UNIT={u}"] + UNIT_FLAGS.get(u, []), f"gemm_kernels_u{u}")
-            for u in range(1, 11)]
+            for u in range(1, 10)]
 SOURCES += [("gemm_bf16p.hip", [], None)]
 SOURCES += [("gemm_bf16p.hip", [f"-DQMK_GEMM_UNIT={u}"] + VGPR_ACC, f"gemm_bf16p_u{u}") for u in range(1, 4)]
 

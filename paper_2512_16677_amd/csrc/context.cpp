@@ -625,7 +625,11 @@ Prec product_prec(qmk_ctx ctx, GemmKind kind) {
 
 qmk_status pick_tile(qmk_ctx ctx, const GemmProblem& pb, hipStream_t s,
                      const std::function<hipError_t(int)>& enqueue, int* cfg) {
-  const int forced = ctx->forced_tile[static_cast<int>(pb.kind)];
+  int forced = ctx->forced_tile[static_cast<int>(pb.kind)];
+  if (forced >= 0 && pb.kind == GemmKind::kJastrow) {
+    *cfg = forced % num_tiles(pb.kind, pb.prec);  // a table of its own, shorter than the FP64 one
+    return QMK_OK;
+  }
   if (forced >= 0) {
     // a tile forced under another precision mode may not exist in this one
     if (forced >= gemm_num_tiles(pb.prec) || !tile_feasible(pb.prec, forced))
@@ -1103,10 +1107,10 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
   const int64_t nn = ctx->nucl_num, nw = ctx->walk_num, ne = ctx->elec_num, P = ctx->P();
   for (int64_t i = 0; i < n_terms * nn; ++i)
     if (!std::isfinite(c[i])) return fail(ctx, QMK_NONFINITE, "non-finite Jastrow coefficient");
-  // m >= 1 needs k <= nord-2 and m <= nord/2 (the product's splits and
-  // rows); m = 0 needs k >= 1 (handled per electron)
-  const int nsplit = static_cast<int>(nord - 1), mh = static_cast<int>(nord / 2), deg = static_cast<int>(nord);
-  const size_t nq = static_cast<size_t>(nsplit * mh * nn * kJasCoef);
+  // m >= 1 needs k <= nord-2 and m <= nord/2 (the product's powers and rows;
+  // k = 0 is handled per nucleus); m = 0 needs k >= 1 (handled per electron)
+  const int kmax = static_cast<int>(nord - 2), mh = static_cast<int>(nord / 2), deg = static_cast<int>(nord);
+  const size_t nq = static_cast<size_t>((kmax + 1) * mh * nn * kJasCoef);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (ctx->nuc_xyz_version != ctx->geom_version) {
     QMK_HIP(ctx, ctx->d_nuc_xyz.ensure(static_cast<size_t>(3 * nn) * 8), "alloc nuclei");
@@ -1114,10 +1118,13 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
                            hipMemcpyHostToDevice), "upload nuclei");
     ctx->nuc_xyz_version = ctx->geom_version;
   }
-  const int64_t M = mh * nn;
-  QMK_HIP(ctx, ctx->een_ra.ensure(static_cast<size_t>(P * M) * 8), "alloc rescaled e-n powers");
+  // the product (k, m >= 1) needs m <= (nord - 1) / 2
+  const int mk = static_cast<int>((nord - 1) / 2);
+  // electrons j of both operands padded to whole steps, their rows to 16
+  const int64_t jp = round_up(ne, 16), nnp = round_up(nn, 16), lda = std::max(mk, 1) * nnp, ldb = round_up(ne, 16);
+  QMK_HIP(ctx, ctx->een_ra.ensure(static_cast<size_t>(nw * jp * lda) * 8), "alloc rescaled e-n powers");
   QMK_HIP(ctx, ctx->een_x.ensure(static_cast<size_t>(P * nn) * 8), "alloc rescaled e-n distances");
-  QMK_HIP(ctx, ctx->een_rt.ensure(static_cast<size_t>(nw * ne * ne) * 8), "alloc rescaled e-e distances");
+  QMK_HIP(ctx, ctx->een_rt.ensure(static_cast<size_t>(nw * jp * ldb) * 8), "alloc rescaled e-e distances");
   QMK_HIP(ctx, ctx->een_j0.ensure(static_cast<size_t>(P) * 8), "alloc per-electron parts");
   QMK_HIP(ctx, ctx->een_g0.ensure(static_cast<size_t>(P * 7) * 8), "alloc m = 0 weight sums");
   // the polynomial tables are uploaded only when the coefficients change
@@ -1148,69 +1155,55 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
   }
   double* const d_q = ctx->een_q.as<double>();
   double* const d_q0 = d_q + nq;
-  // per-wave partial sums of the product: slots per (walker, k) for a tile
-  auto slots_of = [&](int cfg) -> int64_t {
-    const TileCfg t = gemm_tile(Prec::kF64, cfg);
-    return (M + t.bm() - 1) / t.bm() * t.wgm * ((ne + t.bn() - 1) / t.bn() * t.wgn);
-  };
-  int64_t slots_max = 1;
-  for (int cfg = 0; cfg < gemm_num_tiles(Prec::kF64); ++cfg) slots_max = std::max(slots_max, slots_of(cfg));
-  QMK_HIP(ctx, ctx->een_part.ensure(static_cast<size_t>(nw * nsplit * slots_max) * 8), "alloc partial sums");
+  // partial sums of a walker: one per nucleus (k = 0), then the product's slots
+  int64_t slots_max = 0;
+  for (int cfg = 0; cfg < een_num_tiles(); ++cfg) slots_max = std::max(slots_max, een_slots(cfg, nn, ne));
+  const int groups = een_groups(static_cast<int>(nord));
+  const int64_t part_ld = nn + groups * slots_max;
+  QMK_HIP(ctx, ctx->een_part.ensure(static_cast<size_t>(nw * part_ld) * 8), "alloc partial sums");
   {
     LaunchTimer lt(ctx, QMK_KERNEL_JASTROW, s);
     const PointArgs pa = point_args(ctx);
-    QMK_HIP(ctx, launch_een_en(pa, ne, ctx->d_nuc_xyz.as<double>(), nn, kappa, mh, ctx->een_ra.as<double>(),
-                               ctx->een_x.as<double>(), s),
+    QMK_HIP(ctx, launch_een_en(pa, ne, ctx->d_nuc_xyz.as<double>(), nn, kappa, mk, ctx->een_ra.as<double>(),
+                               jp, lda, nnp, ctx->een_x.as<double>(), s),
             "Jastrow e-n distances");
     QMK_HIP(ctx, launch_een_ee(pa, ne, nn, kappa, static_cast<int>(nord), ctx->een_x.as<double>(), d_q0,
-                               ctx->een_g0.as<double>(), ctx->een_rt.as<double>(), ctx->een_j0.as<double>(), s),
-            "Jastrow e-e distances");
+                               ctx->een_g0.as<double>(), ctx->een_rt.as<double>(), jp, ldb, ctx->een_j0.as<double>(), d_q,
+                               ctx->een_part.as<double>(), part_ld, s),
+            "Jastrow e-e distances and k = 0 terms");
   }
-  // part[w, k][slot] = weighted sums over the slot's outputs of
-  //   P^{k,m}[(m-1) nn + a][i] = sum_j Ra[w][j][(m-1) nn + a] rt[w][j][i]^k
-  //   (rt symmetric; the product takes the power as it stages rt)
-  GemmArgs ga{};
-  ga.A = ctx->een_ra.p;
-  ga.sAi = 1;
-  ga.sAl = M;
-  ga.oAc = ne * M;
-  ga.oAs = 0;
-  ga.B = ctx->een_rt.p;
-  ga.sBl = ne;
-  ga.sBj = 1;
-  ga.oBc = ne * ne;
-  ga.oBs = 0;
-  ga.D = ctx->een_part.p;
-  ga.M = M;
-  ga.N = ne;
-  ga.L = nsplit * ne;  // split s = k runs over j in [0, ne) of rt, to the power k
-  ga.Lchunk = ne;
-  ga.nsplit = nsplit;
-  ga.nbatch = static_cast<int32_t>(nw);
-  ga.map_slab = 1;
-  ga.jx = ctx->een_x.as<double>();
-  ga.jq = d_q;
-  ga.j_nn = nn;
-  ga.j_mh = mh;
+  // weighted sums of P^{k,m}_{ia} for k, m >= 1
+  JasArgs ja{};
+  ja.ra = ctx->een_ra.as<double>();
+  ja.rt = ctx->een_rt.as<double>();
+  ja.x = ctx->een_x.as<double>();
+  ja.q = d_q;
+  ja.part = ctx->een_part.as<double>() + nn;
+  ja.nw = nw;
+  ja.ne = ne;
+  ja.nn = nn;
+  ja.nnp = nnp;
+  ja.jp = jp;
+  ja.lda = lda;
+  ja.ldb = ldb;
+  ja.part_ld = part_ld;
+  ja.mh = mh;
   auto enqueue = [&](int cfg) -> hipError_t {
-    GemmArgs gc = ga;
-    gc.oDz = slots_of(cfg);
-    hipError_t e;
-    {
+    if (groups > 0) {
       LaunchTimer lt(ctx, QMK_KERNEL_JASTROW_P, s);
-      e = launch_gemm_jastrow(cfg, gc, s);
+      const hipError_t e = launch_een_product(cfg, static_cast<int>(nord), ja, s);
+      if (e != hipSuccess) return e;
     }
-    if (e != hipSuccess) return e;
     LaunchTimer lt(ctx, QMK_KERNEL_JASTROW, s);
-    return launch_een_finish(ctx->een_part.as<double>(), nsplit * gc.oDz, ctx->een_j0.as<double>(), nw, ne,
-                             j_een, s);
+    return launch_een_finish(ctx->een_part.as<double>(), nn + groups * een_slots(cfg, nn, ne), part_ld,
+                             ctx->een_j0.as<double>(), nw, ne, j_een, s);
   };
-  // tuning key: the product's size and its batch count (walkers x powers),
-  // which decides how many tiles there are to spread over the CUs
-  GemmProblem pb{GemmKind::kJastrow, Prec::kF64, 0, 0, M, ne, ne};
-  pb.nbatch = static_cast<int>(std::min<int64_t>(nw * nsplit, 0x7fffffff));
+  // tuning key: the product's size, the order and the walkers, which decide
+  // how many tiles there are to spread over the CUs
+  GemmProblem pb{GemmKind::kJastrow, Prec::kF64, static_cast<int>(nord), 0, nn, ne, ne};
+  pb.nbatch = static_cast<int>(std::min<int64_t>(nw, 0x7fffffff));
   int cfg = 0;
-  if ((st = pick_tile(ctx, pb, s, enqueue, &cfg)) != QMK_OK) return st;
+  if (groups > 0 && (st = pick_tile(ctx, pb, s, enqueue, &cfg)) != QMK_OK) return st;
   QMK_HIP(ctx, enqueue(cfg), "Jastrow product");
   return QMK_OK;
 }

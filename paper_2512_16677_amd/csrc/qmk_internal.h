@@ -159,18 +159,6 @@ struct GemmArgs {
   const uint32_t* act;
   const int32_t* perm;
   int64_t act_words;
-  // Three-body Jastrow product only (FP64, batch c = walker, split s = power
-  // k of the rescaled e-e distances rt, which B holds with the diagonal
-  // marked < 0): row i of the product is (m = 1 + i / j_nn, nucleus
-  // a = i % j_nn), column j an electron.  jx[c][a][j] holds
-  // x = exp(-kappa |r_j - R_a|) (N per nucleus), jq[s][m-1][a][0..kJasCoef)
-  // the coefficients (ascending powers, zero-padded) of the polynomial in x
-  // that weighs output (i, j).  Each wave stores the weighted sum of its
-  // outputs in its own slot of D (see the product's epilogue).
-  const double* jx;
-  const double* jq;
-  int64_t j_nn;
-  int32_t j_mh;
 };
 
 // Tile of workgroup `bid` of a grid launch; false if it has none.  The
@@ -277,16 +265,36 @@ hipError_t launch_sort_points(const PointArgs& pts, const double* nuc_xyz, int64
 // Determinants det[b] and adjugates adj[b] (row-major n x n) of a batch of
 // row-major n x n FP64 matrices, 1 <= n <= 32.
 hipError_t launch_det_adj(int n, int64_t batch, const double* A, double* det, double* adj, hipStream_t s);
-// Three-body Jastrow pieces (jastrow_kernels.hip; see there for layouts).
-hipError_t launch_een_en(const PointArgs& pts, int64_t ne, const double* nuc, int64_t nn, double kappa, int mh,
-                         double* ra, double* x, hipStream_t s);
-// g0: scratch of 7 doubles per point.
+// Three-body Jastrow pieces (jastrow_kernels.hip; see there for layouts).  ra
+// and rt have jp rows (electrons j) per walker, jp a multiple of 16, the rows
+// from ne on zero, and row lengths lda and ldb; ra holds mk powers, nnp >= nn
+// columns apart.
+hipError_t launch_een_en(const PointArgs& pts, int64_t ne, const double* nuc, int64_t nn, double kappa, int mk,
+                         double* ra, int64_t jp, int64_t lda, int64_t nnp, double* x, hipStream_t s);
+// g0: scratch of 7 doubles per point.  part[w * part_ld + a] receives the k = 0,
+// m >= 1 terms of walker w and nucleus a (weights q[0][m - 1][a][0 .. kJasCoef)).
 hipError_t launch_een_ee(const PointArgs& pts, int64_t ne, int64_t nn, double kappa, int nord, const double* x,
-                         const double* q0, double* g0, double* rt, double* j0, hipStream_t s);
-hipError_t launch_een_finish(const double* part, int64_t slots, const double* j0, int64_t nw, int64_t ne,
-                             double* J, hipStream_t s);
-// The Jastrow product with its fused weighted reduction (FP64).
-hipError_t launch_gemm_jastrow(int cfg, const GemmArgs& g, hipStream_t s);
+                         const double* q0, double* g0, double* rt, int64_t jp, int64_t ldb, double* j0,
+                         const double* q, double* part, int64_t part_ld, hipStream_t s);
+// part: slots values per walker, part_ld apart.
+hipError_t launch_een_finish(const double* part, int64_t slots, int64_t part_ld, const double* j0, int64_t nw,
+                             int64_t ne, double* J, hipStream_t s);
+// The Jastrow product with its fused weighted reduction (jastrow_product.hip),
+// for the terms with k, m >= 1 (order 3 and up).  x[w][a][i] (ne per
+// nucleus), q[k][m - 1][a][0 .. kJasCoef) the weights' coefficients (ascending,
+// mh values of m per k).  Walker w's partial sums start at part + w part_ld:
+// een_groups(nord) times een_slots.
+struct JasArgs {
+  const double *ra, *rt, *x, *q;
+  double* part;
+  int64_t nw, ne, nn, nnp, jp, lda, ldb, part_ld;
+  int32_t mh;
+};
+int een_num_tiles();
+TileCfg een_tile(int cfg);
+int64_t een_slots(int cfg, int64_t nn, int64_t ne);
+int een_groups(int nord);
+hipError_t launch_een_product(int cfg, int nord, const JasArgs& g, hipStream_t s);
 // Rows of n values -> rows of ldd values (ldd >= n, a multiple of 4; zeros
 // from n on; dst 16-byte aligned): FP64 -> FP32 (round to nearest), FP64 ->
 // FP64 or FP32 -> FP32.
@@ -346,6 +354,9 @@ struct GemmProblem {
   int nbatch = 5;  // components per product (1: values only)
   int sparse = 0;  // screened forward product
 };
+// Tiles on offer for products of this kind (the Jastrow product has a table of
+// its own).
+int num_tiles(GemmKind kind, Prec prec);
 bool tile_feasible(Prec prec, int cfg);
 int default_tile(const GemmProblem& p);
 // Returns the tile for p, timing every feasible tile through `enqueue` on

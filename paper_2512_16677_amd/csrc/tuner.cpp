@@ -88,6 +88,7 @@ std::string key_of(const GemmProblem& p, int device) {
     << "/o" << p.o32 << "/" << p.M << "x" << p.N << "x" << p.L;
   if (p.nbatch != 5) o << "/b" << p.nbatch;
   if (p.sparse) o << "/s";
+  if (p.kind == GemmKind::kJastrow) o << "/f";  // the tiles of the fused product
   return o.str();
 }
 
@@ -103,12 +104,19 @@ bool tile_feasible(Prec prec, int cfg) {
   return gemm_tile_lds_bytes(prec, cfg) <= 160u * 1024u;
 }
 
+namespace {
+bool usable(const GemmProblem& p, int cfg) {
+  if (cfg < 0 || cfg >= num_tiles(p.kind, p.prec)) return false;
+  return p.kind == GemmKind::kJastrow || tile_feasible(p.prec, cfg);
+}
+}  // namespace
+
 int default_tile(const GemmProblem& p) {
   int best = -1;
   double best_cost = 0.0;
-  for (int c = 0; c < gemm_num_tiles(p.prec); ++c) {
-    if (!tile_feasible(p.prec, c)) continue;
-    const TileCfg t = gemm_tile(p.prec, c);
+  for (int c = 0; c < num_tiles(p.kind, p.prec); ++c) {
+    if (!usable(p, c)) continue;
+    const TileCfg t = p.kind == GemmKind::kJastrow ? een_tile(c) : gemm_tile(p.prec, c);
     const double pm = static_cast<double>((p.M + t.bm() - 1) / t.bm() * t.bm());
     const double pn = static_cast<double>((p.N + t.bn() - 1) / t.bn() * t.bn());
     // padded work, then a mild preference for large tiles (fewer operand loads)
@@ -129,9 +137,7 @@ int choose_tile(const GemmProblem& p, int device, hipStream_t s,
     std::lock_guard<std::mutex> lk(g_mu);
     load_cache_locked();
     auto it = g_cache.find(key);
-    if (it != g_cache.end() && it->second >= 0 && it->second < gemm_num_tiles(p.prec) &&
-        tile_feasible(p.prec, it->second))
-      return it->second;
+    if (it != g_cache.end() && usable(p, it->second)) return it->second;
   }
   int best = default_tile(p);
   if (tuning_enabled()) {
@@ -141,8 +147,8 @@ int choose_tile(const GemmProblem& p, int device, hipStream_t s,
       return best;
     }
     float best_ms = -1.0f;
-    for (int c = 0; c < gemm_num_tiles(p.prec); ++c) {
-      if (!tile_feasible(p.prec, c)) continue;
+    for (int c = 0; c < num_tiles(p.kind, p.prec); ++c) {
+      if (!usable(p, c)) continue;
       hipError_t e = enqueue(c);  // warm-up
       if (e != hipSuccess) continue;
       float t_min = -1.0f;
@@ -180,9 +186,7 @@ int cached_tile(const GemmProblem& p, int device) {
   std::lock_guard<std::mutex> lk(g_mu);
   load_cache_locked();
   auto it = g_cache.find(key);
-  if (it != g_cache.end() && it->second >= 0 && it->second < gemm_num_tiles(p.prec) &&
-      tile_feasible(p.prec, it->second))
-    return it->second;
+  if (it != g_cache.end() && usable(p, it->second)) return it->second;
   return default_tile(p);
 }
 
