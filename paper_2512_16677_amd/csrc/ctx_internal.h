@@ -133,6 +133,8 @@ struct qmk_ctx_s {
   // that order [Kp][5][Pp] and its activity bitmap, valid at aos_date
   bool sparse = false;
   DevBuf d_sort_key, d_sort_scratch, d_perm, d_act, aos, d_nuc_xyz, w_sorted;
+  DevBuf d_nuc_curve;  // nuclei in the order of a space-filling curve
+  int64_t nuc_curve_version = -1;
   // bitmap of the previous screened evaluation into aos (swapped with d_act)
   DevBuf d_act_prev;
   int64_t aos_Pp = 0, aos_Kp = 0, aos_date = -1, act_words = 0, nuc_xyz_version = -1;
