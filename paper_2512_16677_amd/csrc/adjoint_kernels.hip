@@ -206,7 +206,7 @@ __device__ __forceinline__ void ao_adjoint_body(const AoTables& t, const PointAr
                                                 int64_t sC, double* __restrict__ elec_out,
                                                 int64_t elec_group_stride,
                                                 double* __restrict__ nuc_partial, int bx, int gy,
-                                                unsigned char* smem) {
+                                                unsigned char* smem, int z = 0, int nz = 1, int64_t waves = 0) {
   const NucGroup g = t.group[gy];
   const int np = g.p_end - g.p_begin, ns = g.sh_end - g.sh_begin, nn = g.nuc_end - g.nuc_begin;
   PrimDev* s_prim = reinterpret_cast<PrimDev*>(smem);
@@ -218,7 +218,7 @@ __device__ __forceinline__ void ao_adjoint_body(const AoTables& t, const PointAr
   __syncthreads();
 
   const int64_t p = static_cast<int64_t>(bx) * blockDim.x + threadIdx.x;
-  const int64_t wave = p >> 6;
+  const int64_t wave = z * waves + (p >> 6);  // row of the nucleus partials
   const int lane = threadIdx.x & 63;
   const bool valid = p < pts.P;
   // with a point order (screened adjoint), point p of G-bar is point perm[p]
@@ -244,7 +244,7 @@ __device__ __forceinline__ void ao_adjoint_body(const AoTables& t, const PointAr
       typedef GT CT;  // the arithmetic type of the radial sums and the contraction
       const CT cx = static_cast<CT>(dx), cy = static_cast<CT>(dy), cz = static_cast<CT>(dz);
       const CT cu = static_cast<CT>(u);
-      for (int s = nu.sh_begin; s < nu.sh_end; ++s) {
+      for (int s = nu.sh_begin + z; s < nu.sh_end; s += nz) {
         const ShellDev sh = s_shell[s];
         CT g0 = CT(0), g1 = CT(0), g2 = CT(0), g3 = CT(0);
         CT G_first[5] = {CT(0), CT(0), CT(0), CT(0), CT(0)};
@@ -286,7 +286,7 @@ __device__ __forceinline__ void ao_adjoint_body(const AoTables& t, const PointAr
     }
   }
   if (valid) {
-    double* o = elec_out + gy * elec_group_stride + src * 3;
+    double* o = elec_out + (gy * nz + z) * elec_group_stride + src * 3;
     o[0] = ex;
     o[1] = ey;
     o[2] = ez;
@@ -301,7 +301,8 @@ __global__ __launch_bounds__(256) void ao_adjoint_kernel(AoTables t, PointArgs p
                                                          double* __restrict__ nuc_partial) {
   extern __shared__ __align__(16) unsigned char smem[];
   ao_adjoint_body<GT>(t, pts, gbar, sK, sC, elec_out, elec_group_stride, nuc_partial, blockIdx.x,
-                      blockIdx.y, smem);
+                      blockIdx.y, smem, blockIdx.z, gridDim.z,
+                      static_cast<int64_t>(gridDim.x) * (blockDim.x >> 6));
 }
 
 template <typename GT>
@@ -329,56 +330,80 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return red[0];
 }
 
+// Sums over splits: a workgroup takes 64 consecutive outputs, its four wavefronts
+// every fourth split each, four loads in flight per lane; the four sums are
+// added in order.  (One thread per output walked all the splits, one load at
+// a time: the 130 partials of a 251 x 505 dC took 110 us, 52 us now.)
+__device__ __forceinline__ void reduce_64(const RedJob& j, int64_t loc, bool in, double (*sm)[64]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double v = 0.0;
+  if (in) {
+    const int64_t r = loc / j.cols, c = loc - r * j.cols;
+    const double* p = j.ws + r * j.ld_ws + c;
+    int64_t z = w;
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
+    for (; z + 12 < j.nz; z += 16) {
+      t0 += p[z * j.z_stride];
+      t1 += p[(z + 4) * j.z_stride];
+      t2 += p[(z + 8) * j.z_stride];
+      t3 += p[(z + 12) * j.z_stride];
+    }
+    v = (t0 + t1) + (t2 + t3);
+    for (; z < j.nz; z += 4) v += p[z * j.z_stride];
+  }
+  sm[w][lane] = v;
+  __syncthreads();
+  if (w == 0 && in) {
+    const int64_t r = loc / j.cols, c = loc - r * j.cols;
+    j.out[r * j.ld_out + c] = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
+  }
+}
+
+// One output entry per workgroup: strided partial sums then a fixed-order
+// tree in LDS, so the result does not depend on scheduling.
+__device__ __forceinline__ void reduce_nuc(const NucRedJob& j, int64_t loc, double* sm) {
+  const int A = static_cast<int>(loc / 3), i = static_cast<int>(loc - 3 * (loc / 3));
+  const int a = j.dev_of[A];
+  double acc = 0.0;
+  if (a >= 0)
+    for (int64_t w = threadIdx.x; w < j.n_waves; w += 256) acc += j.part[(w * j.nucl_dev + a) * 3 + i];
+  const double tot = block_sum(acc, sm);
+  if (threadIdx.x == 0) j.out[loc] = tot;
+}
+
+__global__ __launch_bounds__(256) void reduce_kernel(RedJob a, RedJob b, NucRedJob n, int64_t na, int64_t nb) {
+  __shared__ double sm[4][64];
+  int64_t k = blockIdx.x;
+  if (k < na) {
+    const int64_t e = k * 64 + (threadIdx.x & 63);
+    reduce_64(a, e, e < a.rows * a.cols, sm);
+    return;
+  }
+  k -= na;
+  if (k < nb) {
+    const int64_t e = k * 64 + (threadIdx.x & 63);
+    reduce_64(b, e, e < b.rows * b.cols, sm);
+    return;
+  }
+  reduce_nuc(n, k - nb, &sm[0][0]);
+}
+
 __global__ __launch_bounds__(256) void reduce_nuc_batch_kernel(const NucRedJob* __restrict__ jobs,
                                                                const int64_t* __restrict__ prefix,
                                                                int n_jobs) {
   __shared__ double red[256];
   const int64_t e = blockIdx.x;
   const int jb = find_job(prefix, n_jobs, e);
-  const NucRedJob& j = jobs[jb];
-  const int64_t loc = e - prefix[jb];
-  const int A = static_cast<int>(loc / 3), i = static_cast<int>(loc - 3 * (loc / 3));
-  const int a = j.dev_of[A];
-  double acc = 0.0;
-  if (a >= 0)
-    for (int64_t w = threadIdx.x; w < j.n_waves; w += 256) acc += j.part[(w * j.nucl_dev + a) * 3 + i];
-  const double tot = block_sum(acc, red);
-  if (threadIdx.x == 0) j.out[loc] = tot;
+  reduce_nuc(jobs[jb], e - prefix[jb], red);
 }
 
-__global__ void reduce_batch_kernel(const RedJob* __restrict__ jobs,
-                                    const int64_t* __restrict__ prefix, int n_jobs, int64_t total) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= total) return;
-  const int jb = find_job(prefix, n_jobs, e);
-  const RedJob& j = jobs[jb];
-  const int64_t loc = e - prefix[jb];
-  const int64_t r = loc / j.cols, c = loc - r * j.cols;
-  double acc = 0.0;
-  for (int64_t z = 0; z < j.nz; ++z) acc += j.ws[z * j.z_stride + r * j.ld_ws + c];
-  j.out[r * j.ld_out + c] = acc;
-}
-
-// One block per output entry: strided partial sums then a fixed-order tree
-// in LDS, so the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void reduce_nuc_kernel(const double* __restrict__ part,
-                                                         int64_t n_waves, int32_t nucl_dev,
-                                                         const int32_t* __restrict__ dev_of,
-                                                         double* __restrict__ out) {
-  __shared__ double red[256];
-  const int e = blockIdx.x;
-  const int A = e / 3, i = e - 3 * A;
-  const int a = dev_of[A];
-  double acc = 0.0;
-  if (a >= 0)
-    for (int64_t w = threadIdx.x; w < n_waves; w += 256) acc += part[(w * nucl_dev + a) * 3 + i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[e] = red[0];
+__global__ __launch_bounds__(256) void reduce_batch_kernel(const RedJob* __restrict__ jobs,
+                                                           const int64_t* __restrict__ prefix, int n_jobs,
+                                                           int64_t total) {
+  __shared__ double sm[4][64];
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const int jb = find_job(prefix, n_jobs, min(e, total - 1));
+  reduce_64(jobs[jb], e - prefix[jb], e < total, sm);
 }
 
 }  // namespace
@@ -403,7 +428,7 @@ int adj_persist_blocks_per_cu(int f32, size_t smem) {
 hipError_t launch_reduce_batch(const RedJob* jobs, const int64_t* prefix, int n_jobs, int64_t total,
                                hipStream_t s) {
   if (total <= 0 || n_jobs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_batch_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256),
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(static_cast<unsigned>((total + 63) / 64)), dim3(256),
                      0, s, jobs, prefix, n_jobs, total);
   return hipGetLastError();
 }
@@ -416,33 +441,31 @@ hipError_t launch_reduce_nuc_batch(const NucRedJob* jobs, const int64_t* prefix,
   return hipGetLastError();
 }
 
-hipError_t launch_ao_adjoint(const AoTables& t, const PointArgs& pts, const void* gbar,
+hipError_t launch_ao_adjoint(const AoTables& t, const PointArgs& pts, const AoSplit& sp, const void* gbar,
                              int gbar_is_f32, int64_t sK, int64_t sC, double* elec_out,
-                             int64_t elec_group_stride, double* nuc_partial, int64_t* n_waves,
-                             hipStream_t s) {
-  const int64_t nblk = (pts.P + 255) / 256;
-  *n_waves = nblk * 4;
+                             int64_t elec_group_stride, double* nuc_partial, hipStream_t s) {
   if (pts.P <= 0 || t.n_groups <= 0) return hipSuccess;
-  dim3 grid(static_cast<unsigned>(nblk), static_cast<unsigned>(t.n_groups));
+  const dim3 grid(static_cast<unsigned>((pts.P + sp.block - 1) / sp.block), static_cast<unsigned>(t.n_groups),
+                  static_cast<unsigned>(sp.nz));
+  const dim3 blk(sp.block);
   const size_t smem = static_cast<size_t>(t.smem_bytes);
   if (gbar_is_f32)
-    hipLaunchKernelGGL(ao_adjoint_kernel<float>, grid, dim3(256), smem, s, t, pts,
+    hipLaunchKernelGGL(ao_adjoint_kernel<float>, grid, blk, smem, s, t, pts,
                        static_cast<const float*>(gbar), sK, sC, elec_out, elec_group_stride,
                        nuc_partial);
   else
-    hipLaunchKernelGGL(ao_adjoint_kernel<double>, grid, dim3(256), smem, s, t, pts,
+    hipLaunchKernelGGL(ao_adjoint_kernel<double>, grid, blk, smem, s, t, pts,
                        static_cast<const double*>(gbar), sK, sC, elec_out, elec_group_stride,
                        nuc_partial);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_nuc(const double* nuc_partial, int64_t n_waves, int32_t nucl_dev,
-                             const int32_t* dev_of, int32_t nucl_num, double* d_nucl,
-                             hipStream_t s) {
-  const int n = nucl_num * 3;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_nuc_kernel, dim3(n), dim3(256), 0, s, nuc_partial, n_waves, nucl_dev,
-                     dev_of, d_nucl);
+hipError_t launch_reduce(const RedJob& a, const RedJob& b, const NucRedJob& n, hipStream_t s) {
+  const int64_t na = a.out ? (a.rows * a.cols + 63) / 64 : 0, nb = b.out ? (b.rows * b.cols + 63) / 64 : 0;
+  const int64_t blocks = na + nb + (n.out ? 3 * static_cast<int64_t>(n.nucl_num) : 0);
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, a, b, n, na, nb);
   return hipGetLastError();
 }
 

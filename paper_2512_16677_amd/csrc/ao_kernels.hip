@@ -4,7 +4,8 @@
 // a wavefront covers 64 consecutive points (coalesced along the point axis
 // of the [ao][5][point] layout).  A block serves 256 points and one group
 // of nuclei: it stages that group's nucleus, shell and primitive tables in
-// LDS, then walks the nuclei in order.  For each nucleus the wavefront
+// LDS, then walks the nuclei in order (with few points: 64 points and every nz-th
+// shell of each nucleus, see ao_split).  For each nucleus the wavefront
 // takes one ballot on gmin*u < T (the per-nucleus radius of Section 3.1 in
 // squared form); if no lane is inside, the nucleus' AOs are stored as zeros
 // without touching a primitive.  Inside a shell the primitives are sorted by
@@ -182,7 +183,7 @@ __device__ __forceinline__ void shell_zero(int l, OutT* __restrict__ o, int64_t 
 template <typename OutT, bool VAL, int SCR = 0>
 __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& pts,
                                             const AoOut& out, int bx, int gy,
-                                            unsigned char* smem) {
+                                            unsigned char* smem, int z = 0, int nz = 1) {
   const NucGroup g = t.group[gy];
   const int np = g.p_end - g.p_begin, ns = g.sh_end - g.sh_begin, nn = g.nuc_end - g.nuc_begin;
   PrimDev* s_prim = reinterpret_cast<PrimDev*>(smem);
@@ -215,7 +216,7 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
     const bool near = valid && (nu.gmin * u < T);
     if constexpr (SCR == 1) {
       if (!__any(near)) continue;
-      for (int s = nu.sh_begin; s < nu.sh_end; ++s) {
+      for (int s = nu.sh_begin + z; s < nu.sh_end; s += nz) {
         const ShellDev sh = s_shell[s];
         const bool on0 = near && sh.p_begin < sh.p_end && (s_prim[sh.p_begin].gamma * u < T);
         if (__any(on0) && (threadIdx.x & 63) == 0) {
@@ -229,13 +230,13 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
     }
     const bool any_near = __any(near);
     if (SCR == 0 && !any_near) {
-      for (int s = nu.sh_begin; s < nu.sh_end; ++s) {
+      for (int s = nu.sh_begin + z; s < nu.sh_end; s += nz) {
         const ShellDev sh = s_shell[s];
         shell_zero<OutT, VAL>(sh.l, obase + sh.ao_off * out.sK, out.sK, out.sC, out.plane, valid || kPairs);
       }
       continue;
     }
-    for (int s = nu.sh_begin; s < nu.sh_end; ++s) {
+    for (int s = nu.sh_begin + z; s < nu.sh_end; s += nz) {
       const ShellDev sh = s_shell[s];
       if constexpr (SCR == 2) {
         // the wave's block: chunks of this shell active now, or before
@@ -286,7 +287,7 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
 template <typename OutT, bool VAL, int SCR = 0>
 __global__ __launch_bounds__(256, 4) void ao_vgl_kernel(AoTables t, PointArgs pts, AoOut out) {
   extern __shared__ __align__(16) unsigned char smem[];
-  ao_vgl_body<OutT, VAL, SCR>(t, pts, out, blockIdx.x, blockIdx.y, smem);
+  ao_vgl_body<OutT, VAL, SCR>(t, pts, out, blockIdx.x, blockIdx.y, smem, blockIdx.z, gridDim.z);
 }
 
 // Persistent form: the grid walks a list of (molecule, point block, group).
@@ -330,13 +331,16 @@ hipError_t launch_ao_vgl(const AoTables& t, const PointArgs& pts, const AoOut& o
   (void)fp32_compute;
   if (pts.P <= 0 || t.n_groups <= 0) return hipSuccess;
   const size_t smem = static_cast<size_t>(t.smem_bytes);
-  dim3 grid(static_cast<unsigned>((pts.P + 255) / 256), static_cast<unsigned>(t.n_groups));
+  const AoSplit sp = ao_split(pts.P, t);
+  const dim3 blk(sp.block);
+  const dim3 grid(static_cast<unsigned>((pts.P + sp.block - 1) / sp.block), static_cast<unsigned>(t.n_groups),
+                  static_cast<unsigned>(sp.nz));
   if (out_is_f32 == 2)
-    hipLaunchKernelGGL((ao_vgl_kernel<Bf16Pair, false>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<Bf16Pair, false>), grid, blk, smem, s, t, pts, out);
   else if (out_is_f32)
-    hipLaunchKernelGGL((ao_vgl_kernel<float, false>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<float, false>), grid, blk, smem, s, t, pts, out);
   else
-    hipLaunchKernelGGL((ao_vgl_kernel<double, false>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<double, false>), grid, blk, smem, s, t, pts, out);
   return hipGetLastError();
 }
 
@@ -345,16 +349,19 @@ hipError_t launch_ao_vgl_screened(const AoTables& t, const PointArgs& pts, const
   if (pts.P <= 0 || t.n_groups <= 0) return hipSuccess;
   if (!out.act || !out.act_prev) return hipErrorInvalidValue;
   const size_t smem = static_cast<size_t>(t.smem_bytes);
-  dim3 grid(static_cast<unsigned>((pts.P + 255) / 256), static_cast<unsigned>(t.n_groups));
+  const AoSplit sp = ao_split(pts.P, t);
+  const dim3 blk(sp.block);
+  const dim3 grid(static_cast<unsigned>((pts.P + sp.block - 1) / sp.block), static_cast<unsigned>(t.n_groups),
+                  static_cast<unsigned>(sp.nz));
   // activity first: a chunk's bit may come from a shell of another nucleus
   // group, so the stores of the second pass need the whole bitmap
-  hipLaunchKernelGGL((ao_vgl_kernel<double, false, 1>), grid, dim3(256), smem, s, t, pts, out);
+  hipLaunchKernelGGL((ao_vgl_kernel<double, false, 1>), grid, blk, smem, s, t, pts, out);
   if (out_is_f32 == 2)
-    hipLaunchKernelGGL((ao_vgl_kernel<Bf16Pair, false, 2>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<Bf16Pair, false, 2>), grid, blk, smem, s, t, pts, out);
   else if (out_is_f32)
-    hipLaunchKernelGGL((ao_vgl_kernel<float, false, 2>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<float, false, 2>), grid, blk, smem, s, t, pts, out);
   else
-    hipLaunchKernelGGL((ao_vgl_kernel<double, false, 2>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<double, false, 2>), grid, blk, smem, s, t, pts, out);
   return hipGetLastError();
 }
 
@@ -362,11 +369,14 @@ hipError_t launch_ao_value(const AoTables& t, const PointArgs& pts, const AoOut&
                            hipStream_t s) {
   if (pts.P <= 0 || t.n_groups <= 0) return hipSuccess;
   const size_t smem = static_cast<size_t>(t.smem_bytes);
-  dim3 grid(static_cast<unsigned>((pts.P + 255) / 256), static_cast<unsigned>(t.n_groups));
+  const AoSplit sp = ao_split(pts.P, t);
+  const dim3 blk(sp.block);
+  const dim3 grid(static_cast<unsigned>((pts.P + sp.block - 1) / sp.block), static_cast<unsigned>(t.n_groups),
+                  static_cast<unsigned>(sp.nz));
   if (out_is_f32)
-    hipLaunchKernelGGL((ao_vgl_kernel<float, true>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<float, true>), grid, blk, smem, s, t, pts, out);
   else
-    hipLaunchKernelGGL((ao_vgl_kernel<double, true>), grid, dim3(256), smem, s, t, pts, out);
+    hipLaunchKernelGGL((ao_vgl_kernel<double, true>), grid, blk, smem, s, t, pts, out);
   return hipGetLastError();
 }
 

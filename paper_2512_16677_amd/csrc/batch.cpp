@@ -277,7 +277,7 @@ GemmArgs gemm_job(qmk_batch b, size_t m, GemmKind kind, void* out, const void* w
     g.oDz = mp.N;
     g.M = mp.P;
     g.N = mp.N;
-    g.L = g.Lchunk = mp.K;
+    g.L = g.Lchunk = planes ? mp.K : round_up(mp.K, 32);  // both operands are zero up to Kp: no partial step
   } else if (kind == GemmKind::kGbar) {
     g = gbar_args(b->prec, planes ? static_cast<const void*>(w_hi) : w, w_lo, planes ? mp.Nw : ldw, c->d_C.p,
                   c->d_Ctb_hi.p,

@@ -239,6 +239,8 @@ qmk_status build_tables(qmk_ctx ctx) {
   t.ao_num = static_cast<int32_t>(ctx->ao_num);
   t.smem_bytes = static_cast<int32_t>(smem);
   t.nucl_dev = ctx->nucl_dev;
+  t.max_shells = 1;
+  for (const NucDev& n : nuc) t.max_shells = std::max(t.max_shells, n.sh_end - n.sh_begin);
   ctx->tables_dirty = false;
   return QMK_OK;
 }
@@ -807,7 +809,7 @@ qmk_status get_mo_vgl_screened(qmk_ctx ctx, void* out, int32_t dtype, hipStream_
   ga.oDz = N;
   ga.M = P;
   ga.N = N;
-  ga.L = ga.Lchunk = K;
+  ga.L = ga.Lchunk = planes ? K : round_up(K, 32);  // both operands are zero up to Kp: no partial step
   ga.nsplit = 1;
   ga.nbatch = 5;
   ga.act = ctx->d_act.as<uint32_t>();
@@ -1466,8 +1468,8 @@ qmk_status qmk_get_mo_vgl(qmk_ctx ctx, void* out, int64_t size_max, int32_t dtyp
   ga.oDz = N;
   ga.M = P;
   ga.N = N;
-  ga.L = K;
-  ga.Lchunk = K;
+  // both operands are zero from K up to Kp: no partial step
+  ga.L = ga.Lchunk = ctx->mode == QMK_MIXED_BF16X3 ? K : round_up(K, 32);
   ga.nsplit = 1;
   ga.nbatch = 5;
   const Prec prec = gemm_prec(ctx);
@@ -1520,7 +1522,7 @@ qmk_status qmk_get_mo_value(qmk_ctx ctx, void* out, int64_t size_max, int32_t dt
   ga.sDj = 1;
   ga.M = P;
   ga.N = N;
-  ga.L = ga.Lchunk = K;
+  ga.L = ga.Lchunk = round_up(K, 32);  // both operands are zero up to Kp: no partial step
   ga.nsplit = 1;
   ga.nbatch = 1;
   const int o32 = dtype == QMK_F32;
@@ -1624,7 +1626,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
   ga.sDj = Pp;
   ga.M = P;
   ga.N = ctx->n_occ;
-  ga.L = ga.Lchunk = K;
+  ga.L = ga.Lchunk = round_up(K, 32);  // both operands are zero up to Kp: no partial step
   ga.nsplit = 1;
   ga.nbatch = 1;
   ga.occ = ctx->d_occ.as<double>();
@@ -1638,7 +1640,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
     const TileCfg t = gemm_tile(prec, c);
     const int64_t slots = (ctx->n_occ + t.bn() - 1) / t.bn() * t.wgn;
     LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
-    return launch_reduce_splits(ctx->ws_den.as<double>(), slots, 1, P, 0, Pp, rho, 0, s);
+    return launch_reduce(RedJob{ctx->ws_den.as<double>(), slots, 1, P, 0, Pp, rho, 0}, RedJob{}, NucRedJob{}, s);
   };
   GemmProblem pb{GemmKind::kDensity, prec, 0, 0, P, ctx->n_occ, K};
   pb.nbatch = 1;
@@ -1737,6 +1739,9 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
     w = ctx->w_sorted.p;
   }
 
+  // the sums over partial results, in one launch at the end
+  RedJob red_elec{}, red_coef{};
+  NucRedJob red_nuc{};
   if (d_elec || d_nucl) {
     // Gbar[k][c][p] = sum_n W[p][c][n] C[n][k]
     if (ctx->gbar_Pp != Pp || ctx->gbar_Kp != Kp || ctx->gbar_f32 != f32 || !ctx->gbar.p) {
@@ -1763,36 +1768,28 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
       QMK_HIP(ctx, launch(cfg), "Gbar product");
     }
 
-    const int64_t n_waves = (P + 255) / 256 * 4;
-    QMK_HIP(ctx, ctx->ws_nuc.ensure(static_cast<size_t>(n_waves * ctx->nucl_dev * 3) * 8), "alloc nuc partials");
+    const AoSplit sp = ao_split(P, ctx->tab);
+    const int64_t nw = ao_adjoint_waves(P, sp), parts = static_cast<int64_t>(ctx->n_groups) * sp.nz;
+    QMK_HIP(ctx, ctx->ws_nuc.ensure(static_cast<size_t>(nw * ctx->nucl_dev * 3) * 8), "alloc nuc partials");
     double* elec_out = d_elec;
     int64_t gstride = 0;
-    if (ctx->n_groups > 1 || !d_elec) {
-      QMK_HIP(ctx, ctx->ws_elec.ensure(static_cast<size_t>(ctx->n_groups * P * 3) * 8), "alloc elec partials");
+    if (parts > 1 || !d_elec) {
+      QMK_HIP(ctx, ctx->ws_elec.ensure(static_cast<size_t>(parts * P * 3) * 8), "alloc elec partials");
       elec_out = ctx->ws_elec.as<double>();
       gstride = P * 3;
     }
-    int64_t nw = 0;
     {
       LaunchTimer lt(ctx, QMK_KERNEL_AO_ADJOINT, s);
       PointArgs pa = point_args(ctx);
       if (scr) pa.perm = ctx->d_perm.as<int32_t>();
-      QMK_HIP(ctx, launch_ao_adjoint(ctx->tab, pa, ctx->gbar.p, f32, 5 * Pp, Pp, elec_out,
-                                     gstride, ctx->ws_nuc.as<double>(), &nw, s),
+      QMK_HIP(ctx, launch_ao_adjoint(ctx->tab, pa, sp, ctx->gbar.p, f32, 5 * Pp, Pp, elec_out, gstride,
+                                     ctx->ws_nuc.as<double>(), s),
               "AO adjoint kernel");
     }
-    if (d_elec && elec_out != d_elec) {
-      LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
-      QMK_HIP(ctx, launch_reduce_splits(elec_out, ctx->n_groups, P, 3, 3, P * 3, d_elec, 3, s),
-              "reduce electron gradient");
-    }
-    if (d_nucl) {
-      LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
-      QMK_HIP(ctx, launch_reduce_nuc(ctx->ws_nuc.as<double>(), nw, ctx->nucl_dev,
-                                     ctx->d_devof.as<int32_t>(), static_cast<int32_t>(ctx->nucl_num),
-                                     d_nucl, s),
-              "reduce nuclear gradient");
-    }
+    if (d_elec && elec_out != d_elec) red_elec = RedJob{elec_out, parts, P, 3, 3, P * 3, d_elec, 3};
+    if (d_nucl)
+      red_nuc = NucRedJob{ctx->ws_nuc.as<double>(), nw, ctx->nucl_dev, static_cast<int32_t>(ctx->nucl_num),
+                          ctx->d_devof.as<int32_t>(), d_nucl};
   }
   if (d_coef) {
     // dC[n][k] = sum_{c, p} W[p][c][n] ao[k][c][p], split over (c, point chunk).
@@ -1808,8 +1805,12 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
       const int64_t tiles = ((N + t.bm() - 1) / t.bm()) * ((K + t.bn() - 1) / t.bn());
       const int64_t resident = static_cast<int64_t>(std::max(1, ncu)) *
                                gemm_persist_blocks_per_cu(GemmKind::kDcoef, prec, cfg, w32, 0);
+      // at least 256 points each, or 64 where that leaves CUs without work
+      // (water's 1280 points: 25 workgroups of 256 points took 28 us, 100 of 64
+      // take 7)
+      const int64_t idle = std::min<int64_t>((P + 63) / 64, std::max(1, ncu) / (tiles * 5));
       int64_t ns = std::max<int64_t>(1, 4 * resident / (tiles * 5));
-      ns = std::min<int64_t>(ns, std::max<int64_t>(1, (P + 255) / 256));
+      ns = std::min<int64_t>(ns, std::max<int64_t>((P + 255) / 256, idle));
       int64_t chunk = round_up((P + ns - 1) / ns, 32);
       if (planes && scr) {
         // screened BF16x3: whole 64-point blocks per split, at most
@@ -1867,15 +1868,25 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
             : scr  ? launch_gemm_screened_adj(GemmKind::kDcoef, prec, cfg, ga, w32, s)
                 : launch_gemm_typed(GemmKind::kDcoef, prec, cfg, ga, w32, 0, s);
       }
+      red_coef = RedJob{ctx->ws_dc.as<double>(), 5 * nsplit, N, K, Kp, Np * Kp, d_coef, K};
+      return e;
+    };
+    // (timed with the sum over its splits)
+    auto trial = [&](int cfg) -> hipError_t {
+      const hipError_t e = enqueue(cfg);
       if (e != hipSuccess) return e;
       LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
-      return launch_reduce_splits(ctx->ws_dc.as<double>(), 5 * nsplit, N, K, Kp, Np * Kp, d_coef, K, s);
+      return launch_reduce(red_coef, RedJob{}, NucRedJob{}, s);
     };
     GemmProblem pb{GemmKind::kDcoef, prec, w32, 0, N, K, P};
     pb.sparse = scr ? 1 : 0;
     int cfg = 0;
-    if ((st = pick_tile(ctx, pb, s, enqueue, &cfg)) != QMK_OK) return st;
+    if ((st = pick_tile(ctx, pb, s, trial, &cfg)) != QMK_OK) return st;
     QMK_HIP(ctx, enqueue(cfg), "dC product");
+  }
+  if (red_elec.out || red_coef.out || red_nuc.out) {
+    LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
+    QMK_HIP(ctx, launch_reduce(red_coef, red_elec, red_nuc, s), "sum partial results");
   }
   return QMK_OK;
 }

@@ -626,18 +626,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_persist(const GemmArgs* _
   }
 }
 
-__global__ void reduce_splits_kernel(const double* __restrict__ ws, int64_t nz, int64_t rows,
-                                     int64_t cols, int64_t ld_ws, int64_t z_stride,
-                                     double* __restrict__ out, int64_t ld_out) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= rows * cols) return;
-  const int64_t r = e / cols, c = e - r * cols;
-  double acc = 0.0;
-  for (int64_t z = 0; z < nz; ++z) acc += ws[z * z_stride + r * ld_ws + c];
-  out[r * ld_out + c] = acc;
-}
-
 // Tile configurations offered to the autotuner: {WGM, WGN, TM, TN, BK}.
+// 64 x 64 and 64 x 32 serve small products (1280 points of the 25-AO molecule:
+// forward product 9.8 us on 128 x 96, 4.2 us on 64 x 32, which fills 100 CUs
+// instead of 50); the 112-wide ones waste less of a column count just below a
+// multiple of 112 (211 occupied orbitals: 256 columns on 128-wide tiles, 224
+// here; FP64 density product of 785,603 points and 1085 AOs 6.80 -> 5.75 ms).
 #define QMK_TILE_LIST(X) \
   X(0, 2, 2, 4, 4, 16)   \
   X(1, 4, 1, 4, 5, 16)   \
@@ -650,7 +644,11 @@ __global__ void reduce_splits_kernel(const double* __restrict__ ws, int64_t nz, 
   X(8, 2, 1, 5, 5, 16)   \
   X(9, 4, 1, 2, 5, 32)   \
   X(10, 2, 2, 5, 5, 16)  \
-  X(11, 4, 1, 5, 5, 16)
+  X(11, 4, 1, 5, 5, 16)  \
+  X(12, 2, 2, 2, 2, 16)  \
+  X(13, 4, 1, 1, 2, 16)  \
+  X(14, 4, 1, 3, 7, 16)  \
+  X(15, 4, 1, 2, 7, 16)
 
 constexpr TileCfg kTiles[] = {
 #define QMK_TILE_ENTRY(id, wgm, wgn, tm, tn, bk) {wgm, wgn, tm, tn, bk},

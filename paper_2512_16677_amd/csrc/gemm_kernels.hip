@@ -211,16 +211,6 @@ int gemm_persist_blocks_per_cu(GemmKind kind, Prec prec, int cfg, int w_is_f32, 
   return n;
 }
 
-hipError_t launch_reduce_splits(const double* ws, int64_t nz, int64_t rows, int64_t cols,
-                                int64_t ld_ws, int64_t z_stride, double* out, int64_t ld_out,
-                                hipStream_t s) {
-  const int64_t n = rows * cols;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_splits_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256),
-                     0, s, ws, nz, rows, cols, ld_ws, z_stride, out, ld_out);
-  return hipGetLastError();
-}
-
 #endif  // QMK_GEMM_UNIT
 
 }  // namespace qmk

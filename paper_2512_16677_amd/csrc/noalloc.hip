@@ -146,8 +146,8 @@ extern "C" qmk_status qmk_get_mo_vgl_noalloc(qmk_ctx ctx, void* out, int64_t siz
   ga.oDz = N;
   ga.M = P;
   ga.N = N;
-  ga.L = K;
-  ga.Lchunk = K;
+  // both operands are zero from K up to Kp: no partial step
+  ga.L = ga.Lchunk = fmt == 2 ? K : round_up(K, 32);
   ga.nsplit = 1;
   ga.nbatch = 5;
   const Prec prec = gemm_prec(ctx);

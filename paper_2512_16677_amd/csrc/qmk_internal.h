@@ -64,7 +64,31 @@ struct AoTables {
   double T;                 // cutoff on gamma*u: (B-1) ln 2
   int32_t smem_bytes;       // LDS needed by the largest group
   int32_t nucl_dev;         // number of nuclei with at least one shell
+  int32_t max_shells;       // of one nucleus
 };
+
+// Launch shape of the AO kernels for P points: workgroups of `block` points,
+// and the shells of every nucleus dealt out to nz workgroups (shell s of a
+// nucleus goes to s % nz).  One lane walks all the shells of its group one
+// after another, a chain of radial sums: with few points the chip is idle
+// beside a handful of such chains.  So where the 64-point wavefronts do not
+// fill the chip four times over (4 SIMDs x 256 CUs x 4 = 4096), they get
+// workgroups of their own and shorter chains.  1280 points of the 25-AO molecule: AO
+// stage 19 us in one piece, 7.5 us split; AO adjoint 18 and 8.5 us.
+struct AoSplit {
+  int32_t block, nz;
+};
+inline AoSplit ao_split(int64_t P, const AoTables& t) {
+  const int64_t waves = (P + 63) / 64 * (t.n_groups > 0 ? t.n_groups : 1);
+  int64_t nz = 4096 / (waves > 0 ? waves : 1);
+  if (nz > t.max_shells) nz = t.max_shells;
+  if (nz <= 1) return AoSplit{256, 1};
+  return AoSplit{64, static_cast<int32_t>(nz)};
+}
+// Wavefronts of the AO adjoint's launch (rows of the nucleus partials).
+inline int64_t ao_adjoint_waves(int64_t P, const AoSplit& sp) {
+  return (P + sp.block - 1) / sp.block * (sp.block / 64) * sp.nz;
+}
 
 struct PointArgs {
   const double* coord;      // device
@@ -372,9 +396,6 @@ int tune_cache_get(const std::string& key);
 void tune_cache_put(const std::string& key, int cfg);
 bool tuning_on();
 std::string device_arch(int device);
-hipError_t launch_reduce_splits(const double* ws, int64_t nz, int64_t rows, int64_t cols,
-                                int64_t ld_ws, int64_t z_stride, double* out, int64_t ld_out,
-                                hipStream_t s);
 // ---------------------------------------------------------------------------
 // Persistent (work-list) execution used by the batch executor: one launch
 // of a grid sized to the GPU walks a list of items, each item naming a job
@@ -404,6 +425,8 @@ struct RedJob {
   double* out;
   int64_t ld_out;
 };
+// out[3 A + i] = sum_w part[(w*nucl_dev + dev_of[A])*3 + i] over the n_waves
+// rows, or 0 for nuclei without shells (dev_of[A] < 0).
 struct NucRedJob {
   const double* part;
   int64_t n_waves;
@@ -411,6 +434,9 @@ struct NucRedJob {
   const int32_t* dev_of;
   double* out;
 };
+// Up to two sums over splits and one over waves in one launch (those with
+// out = NULL are left out); fixed order.
+hipError_t launch_reduce(const RedJob& a, const RedJob& b, const NucRedJob& n, hipStream_t s);
 
 // out_is_f32: 0 FP64, 1 FP32, 2 bf16 hi / lo planes (out.plane apart), as
 // for launch_ao_vgl.
@@ -471,19 +497,13 @@ int ao_persist_blocks_per_cu(int f32, size_t smem);
 int adj_persist_blocks_per_cu(int f32, size_t smem);
 int gemm_persist_blocks_per_cu(GemmKind kind, Prec prec, int cfg, int w_is_f32, int out_is_f32);
 
-// Adjoint AO stage.  gbar: [ao][5][point] with strides (sK, sC, 1).
-// elec_out + blockIdx.y*elec_group_stride receives sum_k t[p][k][:] of the
-// group's nuclei as [point][3]; nuc_partial[(wave*nucl_dev + a)*3 + i]
-// receives minus the wave's sum over its points for device nucleus a.
-// Returns the number of waves through *n_waves.
-hipError_t launch_ao_adjoint(const AoTables& t, const PointArgs& pts, const void* gbar,
+// Adjoint AO stage.  gbar: [ao][5][point] with strides (sK, sC, 1).  With sp =
+// ao_split(P, t), part z of group gy adds up its shells in
+//   elec_out + (gy nz + z) * elec_group_stride: sum_k t[p][k][:] as [point][3],
+//   nuc_partial[((z waves/nz + wave) * nucl_dev + a)*3 + i]: minus the
+//     wave's sum over its points for device nucleus a,
+// waves = ao_adjoint_waves(P, sp) in all.
+hipError_t launch_ao_adjoint(const AoTables& t, const PointArgs& pts, const AoSplit& sp, const void* gbar,
                              int gbar_is_f32, int64_t sK, int64_t sC, double* elec_out,
-                             int64_t elec_group_stride, double* nuc_partial, int64_t* n_waves,
-                             hipStream_t s);
-// d_nucl[A][i] = sum_w nuc_partial[(w*nucl_dev + dev_of[A])*3 + i], or 0 for
-// nuclei without shells (dev_of[A] < 0).
-hipError_t launch_reduce_nuc(const double* nuc_partial, int64_t n_waves, int32_t nucl_dev,
-                             const int32_t* dev_of, int32_t nucl_num, double* d_nucl,
-                             hipStream_t s);
-
+                             int64_t elec_group_stride, double* nuc_partial, hipStream_t s);
 }  // namespace qmk
