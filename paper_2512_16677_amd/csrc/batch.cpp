@@ -132,34 +132,69 @@ void drop_graph(qmk_batch b) {
 }
 
 // Work list of one product for tile `cfg`: (molecule, M tile, N tile, z),
-// longest reduction first.
+// longest reduction first.  Consecutive workgroups land on the eight XCDs in
+// turn, so entry i belongs to XCD i % 8 (the grid is a multiple of eight where
+// the list is longer than it): tiles that read the same rows of the large
+// operand -- one M tile of AO values (forward), one N tile of weights (W C
+// product), one chunk of points (W^T ao product) -- form a group, and each
+// group goes as a whole to the XCD with the least work so far, so that its
+// operand is read into one L2 instead of eight.  Shorter lists are filled up
+// with empty entries (job -1).  24 molecules
+// of 75 to 560 AOs in FP64: W^T ao product 4.10 ms with the tiles dealt out one by
+// one, 3.53 so; W C product 3.57 and 3.41 ms, forward 3.07 and 3.00 ms; 48
+// molecules in BF16x3: 1.78 and 1.39, 1.58 and 1.49, 1.33 and 1.27 ms.
 std::vector<WorkItem> gemm_items(qmk_batch b, GemmKind kind, int cfg) {
+  constexpr int kXcds = 8;
   const TileCfg t = gemm_tile(b->prec, cfg);
-  struct Key {
-    int64_t cost;
-    WorkItem it;
+  struct Group {
+    int64_t cost;  // of one item: its reduction length
+    int32_t m, i, j, z;  // -1: all tiles of that index
+    int64_t n;
   };
-  std::vector<Key> v;
-  for (size_t m = 0; m < b->plan.size(); ++m) {
-    const MolPlan& mp = b->plan[m];
-    int64_t M, N, L, nz;
+  std::vector<Group> groups;
+  auto tiles = [&](const MolPlan& mp, int64_t* nM, int64_t* nN) {
+    const int64_t M = kind == GemmKind::kForward ? mp.P : (kind == GemmKind::kGbar ? mp.K : mp.N);
+    const int64_t N = kind == GemmKind::kForward ? mp.N : (kind == GemmKind::kGbar ? mp.P : mp.K);
+    *nM = (M + t.bm() - 1) / t.bm();
+    *nN = (N + t.bn() - 1) / t.bn();
+  };
+  for (size_t k = 0; k < b->plan.size(); ++k) {
+    const MolPlan& mp = b->plan[k];
+    const int32_t m = static_cast<int32_t>(k);
+    int64_t nM, nN;
+    tiles(mp, &nM, &nN);
     if (kind == GemmKind::kForward) {
-      M = mp.P; N = mp.N; L = mp.K; nz = 5;
-    } else if (kind == GemmKind::kGbar) {
-      M = mp.K; N = mp.P; L = mp.N; nz = 5;  // rows k, columns p (gbar_args)
+      for (int32_t z = 0; z < 5; ++z)
+        for (int64_t i = 0; i < nM; ++i) groups.push_back({mp.K, m, static_cast<int32_t>(i), -1, z, nN});
+    } else if (kind == GemmKind::kGbar) {  // rows k, columns p (gbar_args)
+      for (int32_t z = 0; z < 5; ++z)
+        for (int64_t j = 0; j < nN; ++j) groups.push_back({mp.N, m, -1, static_cast<int32_t>(j), z, nM});
     } else {
-      M = mp.N; N = mp.K; L = mp.chunk; nz = 5 * mp.nsplit;
+      for (int32_t z = 0; z < 5 * mp.nsplit; ++z) {
+        const int64_t s = z % mp.nsplit;
+        groups.push_back({std::min(mp.chunk, mp.P - s * mp.chunk), m, -1, -1, z, nM * nN});
+      }
     }
-    const int64_t nM = (M + t.bm() - 1) / t.bm(), nN = (N + t.bn() - 1) / t.bn();
-    for (int64_t z = 0; z < nz; ++z)
-      for (int64_t i = 0; i < nM; ++i)
-        for (int64_t j = 0; j < nN; ++j)
-          v.push_back({L, WorkItem{static_cast<int32_t>(m), static_cast<int32_t>(i),
-                                   static_cast<int32_t>(j), static_cast<int32_t>(z)}});
   }
-  std::stable_sort(v.begin(), v.end(), [](const Key& a, const Key& c) { return a.cost > c.cost; });
-  std::vector<WorkItem> out(v.size());
-  for (size_t i = 0; i < v.size(); ++i) out[i] = v[i].it;
+  std::stable_sort(groups.begin(), groups.end(), [](const Group& a, const Group& c) { return a.cost > c.cost; });
+  std::vector<WorkItem> lists[kXcds];
+  int64_t load[kXcds] = {};
+  for (const Group& g : groups) {
+    const int x = static_cast<int>(std::min_element(load, load + kXcds) - load);
+    // every item also pays for its first loads and its stores: about eight K
+    // steps' worth
+    load[x] += (g.cost + 128) * g.n;
+    int64_t nM, nN;
+    tiles(b->plan[g.m], &nM, &nN);
+    for (int64_t i = g.i < 0 ? 0 : g.i; i < (g.i < 0 ? nM : g.i + 1); ++i)
+      for (int64_t j = g.j < 0 ? 0 : g.j; j < (g.j < 0 ? nN : g.j + 1); ++j)
+        lists[x].push_back(WorkItem{g.m, static_cast<int32_t>(i), static_cast<int32_t>(j), g.z});
+  }
+  size_t longest = 0;
+  for (const auto& l : lists) longest = std::max(longest, l.size());
+  std::vector<WorkItem> out(longest * kXcds, WorkItem{-1, 0, 0, 0});
+  for (int x = 0; x < kXcds; ++x)
+    for (size_t i = 0; i < lists[x].size(); ++i) out[i * kXcds + x] = lists[x][i];
   return out;
 }
 

@@ -663,6 +663,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, DEPTH < 0 ? 2 : 1) void gemm_bf16p_
   __shared__ int s_n;
   for (int i = blockIdx.x; i < n_items; i += gridDim.x) {
     const WorkItem it = items[i];
+    if (it.job < 0) continue;  // filler of the list
     bf16p_body<A_MN, TD, WGM, WGN, TM, TN, DEPTH, 0, false>(jobs[it.job], it.a, it.b, it.c, sm, s_list, &s_n);
     __syncthreads();  // LDS is restaged by the next item
   }

@@ -621,6 +621,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_persist(const GemmArgs* _
   __shared__ GemmSmem<T, 16 * WGM * TM, 16 * WGN * TN, BK> sm;
   for (int i = blockIdx.x; i < n_items; i += gridDim.x) {
     const WorkItem it = items[i];
+    if (it.job < 0) continue;  // filler of the list
     gemm_body<T, TA, TB, TD, WGM, WGN, TM, TN, BK, A_I, B_J>(jobs[it.job], it.a, it.b, it.c, sm);
     __syncthreads();
   }

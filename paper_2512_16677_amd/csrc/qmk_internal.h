@@ -401,7 +401,7 @@ std::string device_arch(int device);
 // of a grid sized to the GPU walks a list of items, each item naming a job
 // (one molecule's arguments) and the block coordinates it stands for.
 struct WorkItem {
-  int32_t job, a, b, c;  // AO stages: a = point block, b = nucleus group;
+  int32_t job, a, b, c;  // job < 0 (products): nothing to do; AO stages: a = point block, b = nucleus group;
                          // products: a = M tile, b = N tile, c = batch index z
 };
 struct AoJob {
