@@ -19,6 +19,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import math
 import os
 from typing import Dict, Optional
 
@@ -144,8 +145,13 @@ def _ptr(a):
 
 def _stream(stream=None):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        # the current stream's handle without building a Stream object (2 us)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return ctypes.c_void_p(raw(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 class Context:
@@ -258,7 +264,7 @@ class Context:
                 raise ValueError("coordinates must have shape [walk, elec, 3]")
             walk_num, elec_num = shape[0], shape[1]
         # the library reads 3 walk_num elec_num values through a plain pointer
-        size = int(np.prod(shape, dtype=np.int64))
+        size = math.prod(shape)
         if size != 3 * int(walk_num) * int(elec_num):
             raise ValueError(f"coordinates hold {size} values, 3 * walk_num * elec_num = "
                              f"{3 * int(walk_num) * int(elec_num)} expected")
@@ -278,9 +284,10 @@ class Context:
 
     # ------------------------------------------------------------------- get
     def dims(self) -> Dict[str, int]:
-        v = [ctypes.c_int64() for _ in range(5)]
-        self._check(self._lib.qmk_get_dims(self._h, *[ctypes.byref(x) for x in v]))
-        return dict(zip(["nucl_num", "ao_num", "mo_num", "walk_num", "elec_num"], [x.value for x in v]))
+        v = (ctypes.c_int64 * 5)()
+        at = ctypes.addressof(v)
+        self._check(self._lib.qmk_get_dims(self._h, at, at + 8, at + 16, at + 24, at + 32))
+        return {"nucl_num": v[0], "ao_num": v[1], "mo_num": v[2], "walk_num": v[3], "elec_num": v[4]}
 
     def launch_count(self) -> int:
         v = ctypes.c_int64()

@@ -62,6 +62,33 @@ hipError_t upload(DevBuf& b, const std::vector<T>& v, hipStream_t s) {
   return hipMemcpyAsync(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
 }
 
+// A table inside the batch's one device buffer of job tables.
+struct TabPtr {
+  void* p = nullptr;
+  template <typename T>
+  T* as() const { return static_cast<T*>(p); }
+};
+
+// Collects the job tables of a run, so that one copy uploads them all (a copy
+// per table was a launch and a gap on the stream for each of thirteen).
+struct TableSet {
+  std::vector<unsigned char> bytes;
+  std::vector<std::pair<TabPtr*, size_t>> at;
+  template <typename T>
+  void add(TabPtr& t, const std::vector<T>& v) {
+    const size_t off = (bytes.size() + 255) / 256 * 256;
+    bytes.resize(off + std::max<size_t>(v.size() * sizeof(T), 16));
+    if (!v.empty()) std::memcpy(bytes.data() + off, v.data(), v.size() * sizeof(T));
+    at.push_back({&t, off});
+  }
+  hipError_t upload(DevBuf& b, hipStream_t s) {
+    const hipError_t e = b.ensure(bytes.size());
+    if (e != hipSuccess) return e;
+    for (auto& a : at) a.first->p = static_cast<unsigned char*>(b.p) + a.second;
+    return hipMemcpyAsync(b.p, bytes.data(), bytes.size(), hipMemcpyHostToDevice, s);
+  }
+};
+
 }  // namespace
 
 struct qmk_batch_s {
@@ -87,8 +114,8 @@ struct qmk_batch_s {
   int tile_w32 = -1, tile_o32 = -1;
   std::vector<WorkItem> g_items[3];
   std::vector<GemmArgs> g_jobs[3];  // host copies of the product job tables
-  DevBuf d_ao_items, d_g_items[3];
-  DevBuf d_ao_jobs, d_adj_jobs, d_g_jobs[3], d_red_jobs, d_red_prefix, d_nred_jobs,
+  DevBuf d_ao_items, d_g_items[3], d_tables;
+  TabPtr d_ao_jobs, d_adj_jobs, d_g_jobs[3], d_red_jobs, d_red_prefix, d_nred_jobs,
       d_nred_prefix, d_split_jobs, d_split_prefix, d_pad_jobs, d_pad_prefix;
   int n_red = 0, n_nred = 0, n_split = 0, n_pad = 0;
   int64_t red_total = 0, nred_total = 0, split_total = 0, pad_total = 0;
@@ -644,22 +671,23 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
       nred_prefix.push_back(nred_prefix.back() + mp.nucl_num * 3);
     }
   }
-  QMK_BHIP(b, upload(b->d_ao_jobs, ao_jobs, s), "upload jobs");
-  QMK_BHIP(b, upload(b->d_g_jobs[0], gj[0], s), "upload jobs");
+  TableSet tables;
+  tables.add(b->d_ao_jobs, ao_jobs);
+  tables.add(b->d_g_jobs[0], gj[0]);
   if (with_adj) {
-    QMK_BHIP(b, upload(b->d_adj_jobs, adj_jobs, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_g_jobs[1], gj[1], s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_g_jobs[2], gj[2], s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_red_jobs, red, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_red_prefix, red_prefix, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_nred_jobs, nred, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_nred_prefix, nred_prefix, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_split_jobs, split, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_split_prefix, split_prefix, s), "upload jobs");
+    tables.add(b->d_adj_jobs, adj_jobs);
+    tables.add(b->d_g_jobs[1], gj[1]);
+    tables.add(b->d_g_jobs[2], gj[2]);
+    tables.add(b->d_red_jobs, red);
+    tables.add(b->d_red_prefix, red_prefix);
+    tables.add(b->d_nred_jobs, nred);
+    tables.add(b->d_nred_prefix, nred_prefix);
+    tables.add(b->d_split_jobs, split);
+    tables.add(b->d_split_prefix, split_prefix);
+    tables.add(b->d_pad_jobs, pads);
+    tables.add(b->d_pad_prefix, pad_prefix);
     b->n_split = static_cast<int>(split.size());
     b->split_total = split_prefix.back();
-    QMK_BHIP(b, upload(b->d_pad_jobs, pads, s), "upload jobs");
-    QMK_BHIP(b, upload(b->d_pad_prefix, pad_prefix, s), "upload jobs");
     b->n_pad = static_cast<int>(pads.size());
     b->pad_total = pad_prefix.back();
     b->n_red = static_cast<int>(red.size());
@@ -667,6 +695,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
     b->n_nred = static_cast<int>(nred.size());
     b->nred_total = nred_prefix.back();
   }
+  QMK_BHIP(b, tables.upload(b->d_tables, s), "upload jobs");
 
   for (int k = 0; k < 3; ++k) b->g_jobs[k] = gj[k];
 

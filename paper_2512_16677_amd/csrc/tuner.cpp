@@ -77,19 +77,32 @@ void save_cache_locked() {
   std::rename(tmp.c_str(), path);
 }
 
+// Architecture name of a device ("gfx950"), asked for once.
+const std::string& arch_of(int device) {
+  constexpr int kMaxDevices = 64;
+  static std::mutex mu;
+  static std::string name[kMaxDevices + 1];
+  std::lock_guard<std::mutex> lk(mu);
+  std::string& n = name[device >= 0 && device < kMaxDevices ? device : kMaxDevices];
+  if (n.empty() || device < 0 || device >= kMaxDevices) {
+    hipDeviceProp_t prop;
+    std::string arch = "gfx?";
+    if (hipGetDeviceProperties(&prop, device) == hipSuccess) arch = prop.gcnArchName;
+    const size_t colon = arch.find(':');
+    n = colon == std::string::npos ? arch : arch.substr(0, colon);
+  }
+  return n;
+}
+
 std::string key_of(const GemmProblem& p, int device) {
-  hipDeviceProp_t prop;
-  std::string arch = "gfx?";
-  if (hipGetDeviceProperties(&prop, device) == hipSuccess) arch = prop.gcnArchName;
-  const size_t colon = arch.find(':');
-  if (colon != std::string::npos) arch = arch.substr(0, colon);
-  std::ostringstream o;
-  o << arch << "/k" << static_cast<int>(p.kind) << "/p" << static_cast<int>(p.prec) << "/w" << p.w32
-    << "/o" << p.o32 << "/" << p.M << "x" << p.N << "x" << p.L;
-  if (p.nbatch != 5) o << "/b" << p.nbatch;
-  if (p.sparse) o << "/s";
-  if (p.kind == GemmKind::kJastrow) o << "/f";  // the tiles of the fused product
-  return o.str();
+  char buf[192];
+  int n = std::snprintf(buf, sizeof(buf), "/k%d/p%d/w%d/o%d/%lldx%lldx%lld", static_cast<int>(p.kind),
+                        static_cast<int>(p.prec), p.w32, p.o32, static_cast<long long>(p.M),
+                        static_cast<long long>(p.N), static_cast<long long>(p.L));
+  if (p.nbatch != 5) n += std::snprintf(buf + n, sizeof(buf) - n, "/b%d", p.nbatch);
+  if (p.sparse) n += std::snprintf(buf + n, sizeof(buf) - n, "/s");
+  if (p.kind == GemmKind::kJastrow) std::snprintf(buf + n, sizeof(buf) - n, "/f");  // the fused product's tiles
+  return arch_of(device) + buf;
 }
 
 bool tuning_enabled() {
@@ -206,13 +219,7 @@ void tune_cache_put(const std::string& key, int cfg) {
 
 bool tuning_on() { return tuning_enabled(); }
 
-std::string device_arch(int device) {
-  hipDeviceProp_t prop;
-  std::string arch = "gfx?";
-  if (hipGetDeviceProperties(&prop, device) == hipSuccess) arch = prop.gcnArchName;
-  const size_t colon = arch.find(':');
-  return colon == std::string::npos ? arch : arch.substr(0, colon);
-}
+std::string device_arch(int device) { return arch_of(device); }
 
 void forget_tuning() {
   std::lock_guard<std::mutex> lk(g_mu);
