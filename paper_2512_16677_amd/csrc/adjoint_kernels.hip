@@ -355,7 +355,7 @@ __device__ __forceinline__ void reduce_64(const RedJob& j, int64_t loc, bool in,
   __syncthreads();
   if (w == 0 && in) {
     const int64_t r = loc / j.cols, c = loc - r * j.cols;
-    j.out[r * j.ld_out + c] = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
+    j.out[r * j.ld_out + (j.col ? j.col[c] : c)] = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
   }
 }
 

@@ -570,7 +570,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
     if (st != QMK_OK) return bfail(b, st, "context " + std::to_string(i) + ": " + c->err);
     if (c->cusp_on)
       return bfail(b, QMK_UNSUPPORTED, "context " + std::to_string(i) + " has the cusp correction on");
-    if ((st = ensure_tables(c)) != QMK_OK) return bfail(b, st, c->err);
+    if ((st = ensure_tables(c, s)) != QMK_OK) return bfail(b, st, c->err);
     if ((st = ensure_coef(c, s)) != QMK_OK) return bfail(b, st, c->err);
     key.insert(key.end(), {c->P(), c->ao_num, c->mo_num, c->nucl_num, c->n_groups, c->nucl_dev,
                            static_cast<int64_t>(c->tab.smem_bytes)});
@@ -631,7 +631,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
       if (mp.n_groups > 1) {
         elec_out = static_cast<double*>(b->ws_elec.p) + mp.elec_off;
         gstride = mp.P * 3;
-        red.push_back(RedJob{elec_out, mp.n_groups, mp.P, 3, 3, mp.P * 3, de, 3});
+        red.push_back(RedJob{elec_out, mp.n_groups, mp.P, 3, 3, mp.P * 3, de, 3, nullptr});
         red_prefix.push_back(red_prefix.back() + mp.P * 3);
       }
       adj_jobs[i] = AdjJob{t, pa, static_cast<char*>(b->gbar.p) + mp.gbar_off * b->esz, 5 * mp.Pp,
@@ -663,7 +663,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
       gj[1].push_back(gemm_job(b, i, GemmKind::kGbar, nullptr, wj, ldw, padded));
       gj[2].push_back(gemm_job(b, i, GemmKind::kDcoef, nullptr, wj, ldw, padded));
       red.push_back(RedJob{static_cast<double*>(b->ws_dc.p) + mp.dc_off, 5 * mp.nsplit, mp.N, mp.K,
-                           mp.Kp, mp.Np * mp.Kp, dc, mp.K});
+                           mp.Kp, mp.Np * mp.Kp, dc, mp.K, c->ao_of()});
       red_prefix.push_back(red_prefix.back() + mp.N * mp.K);
       nred.push_back(NucRedJob{static_cast<double*>(b->ws_nuc.p) + mp.nuc_off, mp.n_waves,
                                mp.nucl_dev, static_cast<int32_t>(mp.nucl_num),

@@ -138,16 +138,155 @@ void collect_timing(qmk_ctx ctx) {
   ctx->pending.clear();
 }
 
+// Indices of the nuclei in the order of a Hilbert curve through their bounding
+// cube (1024 cells a side; Skilling's transposed-axes form of the curve, AIP
+// Conf. Proc. 707, 381, 2004).  The screened products read points sorted by
+// nearest nucleus in 128- or 256-point tiles, each of which spans a few
+// nuclei: along the curve these are neighbours, and the tile's list of active
+// AOs is little longer than one nucleus'.  7500 AOs, 63,000 points, B = 24,
+// AO rows in the caller's order: a 256-point tile visits 0.27 of its K steps,
+// 0.35 with the nuclei in the caller's order, and the BF16x3 forward product
+// takes 3.74 ms, 4.85 before.
+std::vector<size_t> curve_order(const std::vector<double>& nucl) {
+  constexpr int kBits = 10;
+  const size_t n = nucl.size() / 3;
+  double lo[3], side = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    double a = nucl[i], b = nucl[i];
+    for (size_t k = 0; k < n; ++k) {
+      a = std::min(a, nucl[3 * k + i]);
+      b = std::max(b, nucl[3 * k + i]);
+    }
+    lo[i] = a;
+    side = std::max(side, b - a);
+  }
+  std::vector<std::pair<uint32_t, size_t>> key(n);
+  for (size_t k = 0; k < n; ++k) {
+    uint32_t x[3];
+    for (int i = 0; i < 3; ++i) {
+      const double t = side > 0.0 ? (nucl[3 * k + i] - lo[i]) / side : 0.0;
+      x[i] = static_cast<uint32_t>(std::min(std::max(0.0, t), 1.0) * ((1 << kBits) - 1));
+    }
+    for (uint32_t q = 1u << (kBits - 1); q > 1; q >>= 1) {
+      const uint32_t p = q - 1;
+      for (int i = 0; i < 3; ++i) {
+        if (x[i] & q) {
+          x[0] ^= p;
+        } else {
+          const uint32_t t = (x[0] ^ x[i]) & p;
+          x[0] ^= t;
+          x[i] ^= t;
+        }
+      }
+    }
+    x[1] ^= x[0];
+    x[2] ^= x[1];
+    uint32_t t = 0;
+    for (uint32_t q = 1u << (kBits - 1); q > 1; q >>= 1)
+      if (x[2] & q) t ^= q - 1;
+    uint32_t h = 0;
+    for (int b = kBits - 1; b >= 0; --b)
+      for (int i = 0; i < 3; ++i) h = (h << 1) | (((x[i] ^ t) >> b) & 1u);
+    key[k] = {h, k};
+  }
+  std::sort(key.begin(), key.end());
+  std::vector<size_t> out(n);
+  for (size_t k = 0; k < n; ++k) out[k] = key[k].second;
+  return out;
+}
+
+// First row of every shell in the context's own AO arrays.  The screened
+// products skip K steps of 32 rows (16 in FP64 and FP32) whose AOs are all
+// zero on a tile of points, so AOs that are active together belong together:
+// shells of similar reach (classes of the smallest exponent), and within a
+// class along the curve through their nuclei.  Few classes mix far and short
+// reaches in one step, many spread a step over more space, so the classes are
+// the ones with the least expected steps for a tile of points: a class of n
+// steps whose farthest reach is r is cut into cubes of side (V / n)^(1/3), and
+// a tile meets those within r of it.  7500 AOs, 63,000 points, B = 24: four
+// classes, and a 256-point tile visits 0.12 of its K steps, 0.27 with the rows
+// in the caller's order, where nearly every step holds a diffuse shell;
+// BF16x3 forward pass 2.5 ms, 4.2 ms in the caller's order.
+std::vector<int64_t> order_rows(qmk_ctx ctx, const std::vector<double>& nucl) {
+  const int64_t S = ctx->shell_num;
+  std::vector<int64_t> order(S), row(S + 1);
+  std::iota(order.begin(), order.end(), int64_t(0));
+  if (ctx->ao_num >= kOrderRowsAo) {
+    const std::vector<size_t> curve = curve_order(nucl);
+    std::vector<int64_t> rank(curve.size());
+    for (size_t i = 0; i < curve.size(); ++i) rank[curve[i]] = static_cast<int64_t>(i);
+    // bins of the smallest exponent, a quarter octave wide, the widest shells first
+    constexpr int kBins = 256;
+    constexpr double kReachArg = 25.0, kTile = 2.0;  // exponent argument at the reach; a tile's extent (bohr)
+    std::vector<double> gmin(S, INFINITY);
+    std::vector<int> bin(S);
+    std::vector<double> rows(kBins, 0.0), reach(kBins, 0.0);
+    for (int64_t s = 0; s < S; ++s) {
+      for (int64_t k = ctx->sh_off[s]; k < ctx->sh_off[s + 1]; ++k) gmin[s] = std::min(gmin[s], ctx->expo[k]);
+      bin[s] = static_cast<int>(std::clamp(4.0 * std::log2(gmin[s]) + kBins / 2, 0.0, kBins - 1.0));
+      rows[bin[s]] += n_cart(ctx->sh_l[s]);
+      if (std::isfinite(gmin[s])) reach[bin[s]] = std::max(reach[bin[s]], std::sqrt(kReachArg / gmin[s]));
+    }
+    double volume = 1.0;
+    for (int x = 0; x < 3; ++x) {
+      double lo = nucl[x], hi = nucl[x];
+      for (size_t i = x; i < nucl.size(); i += 3) {
+        lo = std::min(lo, nucl[i]);
+        hi = std::max(hi, nucl[i]);
+      }
+      volume *= hi - lo + kTile;
+    }
+    std::vector<int> used;
+    for (int i = 0; i < kBins; ++i)
+      if (rows[i] > 0.0) used.push_back(i);
+    // best[j]: expected steps of the first j used bins in their best classes, the last of them from bin from[j]
+    const int n_used = static_cast<int>(used.size());
+    std::vector<double> best(n_used + 1, INFINITY);
+    std::vector<int> from(n_used + 1, 0), cls(kBins, 0);
+    best[0] = 0.0;
+    for (int j = 1; j <= n_used; ++j) {
+      double r = 0.0, n = 0.0;
+      for (int i = j - 1; i >= 0; --i) {
+        r = std::max(r, reach[used[i]]);
+        n += rows[used[i]];
+        const double steps = n / 32.0, side = std::cbrt(volume / steps) + 2.0 * r + kTile;
+        const double met = std::min(steps, steps / volume * side * side * side) + 0.5;  // half a step shared
+        if (best[i] + met < best[j]) {
+          best[j] = best[i] + met;
+          from[j] = i;
+        }
+      }
+    }
+    for (int j = n_used; j > 0; j = from[j])
+      for (int i = from[j]; i < j; ++i) cls[used[i]] = from[j];
+    std::sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
+      if (cls[bin[a]] != cls[bin[b]]) return cls[bin[a]] < cls[bin[b]];
+      const int64_t ra = rank[ctx->sh_nuc[a]], rb = rank[ctx->sh_nuc[b]];
+      if (ra != rb) return ra < rb;
+      if (gmin[a] != gmin[b]) return gmin[a] < gmin[b];
+      return a < b;
+    });
+  }
+  int64_t at = 0;
+  for (int64_t s : order) {
+    row[s] = at;
+    at += n_cart(ctx->sh_l[s]);
+  }
+  row[S] = at;
+  return row;
+}
+
 // Builds the device nucleus / shell / primitive tables and nucleus groups.
-qmk_status build_tables(qmk_ctx ctx) {
+qmk_status build_tables(qmk_ctx ctx, hipStream_t stream, bool* relay) {
   const int64_t S = ctx->shell_num;
   std::vector<std::vector<int64_t>> shells_of(ctx->nucl_num);
   for (int64_t s = 0; s < S; ++s) shells_of[ctx->sh_nuc[s]].push_back(s);
   std::vector<int64_t> ao_off(S + 1, 0);
   for (int64_t s = 0; s < S; ++s) ao_off[s + 1] = ao_off[s] + n_cart(ctx->sh_l[s]);
+  const std::vector<int64_t> row = order_rows(ctx, ctx->nucl);
 
   std::vector<NucDev> nuc;
-  std::vector<ShellDev> shell;
+  std::vector<ShellDev> shell, shell_caller;
   std::vector<PrimDev> prim;
   std::vector<NucGroup> group;
   std::vector<int32_t> dev_of(ctx->nucl_num, -1);
@@ -202,6 +341,8 @@ qmk_status build_tables(qmk_ctx ctx) {
         nd.gmin = std::min(nd.gmin, ctx->expo[k]);
       }
       sd.p_end = static_cast<int32_t>(prim.size()) - cur.p_begin;
+      shell_caller.push_back(sd);
+      sd.ao_off = static_cast<int32_t>(row[s]);
       shell.push_back(sd);
     }
     nd.sh_end = static_cast<int32_t>(shell.size()) - cur.sh_begin;
@@ -223,7 +364,35 @@ qmk_status build_tables(qmk_ctx ctx) {
   QMK_HIP(ctx, up(ctx->d_nuc, nuc.data(), nuc.size() * sizeof(NucDev)), "upload nuclei");
   QMK_HIP(ctx, up(ctx->d_shell, shell.data(), shell.size() * sizeof(ShellDev)), "upload shells");
   QMK_HIP(ctx, up(ctx->d_prim, prim.data(), prim.size() * sizeof(PrimDev)), "upload primitives");
-  QMK_HIP(ctx, up(ctx->d_aofac, ctx->af.data(), ctx->af.size() * sizeof(double)), "upload M");
+  // the rows' AOs; copies of C (and what is derived from them) follow the rows
+  const bool ordered = ctx->ao_num >= kOrderRowsAo;
+  std::vector<int32_t> row_of(ordered ? ctx->ao_num : 0), ao_of(row_of.size());
+  std::vector<double> af = ctx->af;
+  if (ordered)
+    for (int64_t s = 0; s < S; ++s)
+      for (int64_t i = 0; i < n_cart(ctx->sh_l[s]); ++i) {
+        row_of[ao_off[s] + i] = static_cast<int32_t>(row[s] + i);
+        ao_of[row[s] + i] = static_cast<int32_t>(ao_off[s] + i);
+        af[row[s] + i] = ctx->af[ao_off[s] + i];
+      }
+  // copies of C in another order of rows are laid out again; earlier work of
+  // the stream may still read them and the tables
+  const bool reorder = row_of != ctx->row_of;
+  *relay = reorder && !ctx->coef_dirty;
+  if (reorder) {
+    QMK_HIP(ctx, hipStreamSynchronize(stream), "new AO rows");
+    ctx->coef_dirty = true;
+    ctx->occ_coef_version = -1;
+    ctx->row_of = row_of;
+  }
+  ctx->shell_row = row;
+  QMK_HIP(ctx, up(ctx->d_aofac, af.data(), af.size() * sizeof(double)), "upload M");
+  if (ordered) {
+    QMK_HIP(ctx, up(ctx->d_ao_of, ao_of.data(), ao_of.size() * sizeof(int32_t)), "upload AO rows");
+    QMK_HIP(ctx, up(ctx->d_aofac_caller, ctx->af.data(), ctx->af.size() * sizeof(double)), "upload M");
+    QMK_HIP(ctx, up(ctx->d_shell_caller, shell_caller.data(), shell_caller.size() * sizeof(ShellDev)),
+            "upload shells");
+  }
   QMK_HIP(ctx, up(ctx->d_group, group.data(), group.size() * sizeof(NucGroup)), "upload groups");
   QMK_HIP(ctx, up(ctx->d_devof, dev_of.data(), dev_of.size() * sizeof(int32_t)), "upload map");
 
@@ -241,16 +410,12 @@ qmk_status build_tables(qmk_ctx ctx) {
   t.nucl_dev = ctx->nucl_dev;
   t.max_shells = 1;
   for (const NucDev& n : nuc) t.max_shells = std::max(t.max_shells, n.sh_end - n.sh_begin);
-  ctx->tables_dirty = false;
-  return QMK_OK;
-}
-
-qmk_status ensure_tables(qmk_ctx ctx) {
-  if (ctx->tables_dirty) {
-    qmk_status st = build_tables(ctx);
-    if (st != QMK_OK) return st;
+  ctx->tab_caller = t;
+  if (ordered) {
+    ctx->tab_caller.shell = ctx->d_shell_caller.as<ShellDev>();
+    ctx->tab_caller.ao_factor = ctx->d_aofac_caller.as<double>();
   }
-  ctx->tab.T = (ctx->bits - 1) * std::log(2.0);
+  ctx->tables_dirty = false;
   return QMK_OK;
 }
 
@@ -270,14 +435,27 @@ qmk_status make_coef_copies(qmk_ctx ctx, const double* src, hipStream_t s) {
     for (DevBuf* b : {&ctx->d_Cb_hi, &ctx->d_Cb_lo, &ctx->d_Ctb_hi, &ctx->d_Ctb_lo})
       QMK_HIP(ctx, b->ensure(n * 2), "alloc split C");
   const CoefCopies o{ctx->d_C.p, ctx->d_Ct.p, ctx->d_Cb_hi.p, ctx->d_Cb_lo.p, ctx->d_Ctb_hi.p, ctx->d_Ctb_lo.p};
-  QMK_HIP(ctx, launch_coef_layout(src, N, K, ctx->Np, ctx->Kp, want, o, s), "lay out C");
+  QMK_HIP(ctx, launch_coef_layout(src, N, K, ctx->Np, ctx->Kp, want, ctx->ao_of(), o, s), "lay out C");
   QMK_HIP(ctx, hipStreamSynchronize(s), "lay out C");
   ctx->coef_dirty = false;
   ctx->coef_mode = want;
   return QMK_OK;
 }
 
+qmk_status ensure_tables(qmk_ctx ctx, hipStream_t s) {
+  if (ctx->tables_dirty) {
+    bool relay = false;
+    qmk_status st = build_tables(ctx, s, &relay);
+    if (st == QMK_OK && relay && ctx->craw_valid) st = make_coef_copies(ctx, ctx->d_Craw.as<double>(), s);
+    if (st != QMK_OK) return st;
+  }
+  ctx->tab.T = ctx->tab_caller.T = (ctx->bits - 1) * std::log(2.0);
+  return QMK_OK;
+}
+
 qmk_status ensure_coef(qmk_ctx ctx, hipStream_t s) {
+  const qmk_status ts = ensure_tables(ctx, s);  // the order of the copies' rows
+  if (ts != QMK_OK) return ts;
   const int want = ctx->mode == QMK_FP64 ? 0 : (ctx->mode == QMK_MIXED_F32 ? 1 : 2);
   if (!ctx->coef_dirty && ctx->coef_mode == want) return QMK_OK;
   if (!ctx->craw_valid) {
@@ -327,7 +505,7 @@ qmk_status check_ready(qmk_ctx ctx, bool need_coef) {
 // provide(ao_vgl): recompute the AO array iff its time stamp is stale (or
 // `force`: the adjoint with AO retention off).
 qmk_status provide_ao(qmk_ctx ctx, hipStream_t s, bool force = false) {
-  qmk_status st = ensure_tables(ctx);
+  qmk_status st = ensure_tables(ctx, s);
   if (st != QMK_OK) return st;
   // 0: FP64; 1: FP32; 2: bf16 hi and lo planes (BF16x3 mode), same bytes as FP32
   const int f32 = ctx->ao_format();
@@ -354,68 +532,10 @@ qmk_status provide_ao(qmk_ctx ctx, hipStream_t s, bool force = false) {
   return QMK_OK;
 }
 
-// The nuclei in the order of a Hilbert curve through their bounding cube
-// (1024 cells a side; Skilling's transposed-axes form of the curve, AIP Conf.
-// Proc. 707, 381, 2004).  The screened products read points sorted by
-// nearest nucleus in 128- or 256-point tiles, each of which spans a few
-// nuclei: along the curve these are neighbours, and the tile's list of active
-// AOs is little longer than one nucleus'.  7500 AOs, 63,000 points, B = 24: a
-// 256-point tile visits 0.27 of its K steps, 0.35 with the nuclei in the
-// caller's order; the BF16x3 forward
-// product takes 3.74 ms, 4.85 before.
-std::vector<double> along_curve(const std::vector<double>& nucl) {
-  constexpr int kBits = 10;
-  const size_t n = nucl.size() / 3;
-  double lo[3], side = 0.0;
-  for (int i = 0; i < 3; ++i) {
-    double a = nucl[i], b = nucl[i];
-    for (size_t k = 0; k < n; ++k) {
-      a = std::min(a, nucl[3 * k + i]);
-      b = std::max(b, nucl[3 * k + i]);
-    }
-    lo[i] = a;
-    side = std::max(side, b - a);
-  }
-  std::vector<std::pair<uint32_t, size_t>> key(n);
-  for (size_t k = 0; k < n; ++k) {
-    uint32_t x[3];
-    for (int i = 0; i < 3; ++i) {
-      const double t = side > 0.0 ? (nucl[3 * k + i] - lo[i]) / side : 0.0;
-      x[i] = static_cast<uint32_t>(std::min(std::max(t, 0.0), 1.0) * ((1 << kBits) - 1));
-    }
-    for (uint32_t q = 1u << (kBits - 1); q > 1; q >>= 1) {
-      const uint32_t p = q - 1;
-      for (int i = 0; i < 3; ++i) {
-        if (x[i] & q) {
-          x[0] ^= p;
-        } else {
-          const uint32_t t = (x[0] ^ x[i]) & p;
-          x[0] ^= t;
-          x[i] ^= t;
-        }
-      }
-    }
-    x[1] ^= x[0];
-    x[2] ^= x[1];
-    uint32_t t = 0;
-    for (uint32_t q = 1u << (kBits - 1); q > 1; q >>= 1)
-      if (x[2] & q) t ^= q - 1;
-    uint32_t h = 0;
-    for (int b = kBits - 1; b >= 0; --b)
-      for (int i = 0; i < 3; ++i) h = (h << 1) | (((x[i] ^ t) >> b) & 1u);
-    key[k] = {h, k};
-  }
-  std::sort(key.begin(), key.end());
-  std::vector<double> out(nucl.size());
-  for (size_t k = 0; k < n; ++k)
-    for (int i = 0; i < 3; ++i) out[3 * k + i] = nucl[3 * key[k].second + i];
-  return out;
-}
-
 // Screened contraction input: the points sorted by nearest nucleus, the AO
 // array in that order and the (64-point block, 16-AO chunk) activity bitmap.
 qmk_status provide_ao_sorted(qmk_ctx ctx, hipStream_t s, bool force = false) {
-  qmk_status st = ensure_tables(ctx);
+  qmk_status st = ensure_tables(ctx, s);
   if (st != QMK_OK) return st;
   const int f32 = ctx->ao_format();  // 0 FP64, 1 FP32, 2 bf16 hi and lo planes
   const int64_t P = ctx->P(), Pp = round_up(P, kPointPad), Kp = round_up(ctx->ao_num, kAoPad);
@@ -427,7 +547,10 @@ qmk_status provide_ao_sorted(qmk_ctx ctx, hipStream_t s, bool force = false) {
                 "the screened evaluation sorts points by nearest nucleus for at most " +
                     std::to_string(kSortMaxNuclei) + " nuclei");
   if (ctx->nuc_curve_version != ctx->geom_version) {
-    const std::vector<double> xyz = along_curve(ctx->nucl);
+    const std::vector<size_t> order = curve_order(ctx->nucl);
+    std::vector<double> xyz(static_cast<size_t>(3 * nn));
+    for (int64_t k = 0; k < nn; ++k)
+      for (int i = 0; i < 3; ++i) xyz[3 * k + i] = ctx->nucl[3 * order[k] + i];
     QMK_HIP(ctx, ctx->d_nuc_curve.ensure(static_cast<size_t>(3 * nn) * 8), "alloc nuclei");
     QMK_HIP(ctx, hipMemcpy(ctx->d_nuc_curve.p, xyz.data(), static_cast<size_t>(3 * nn) * 8, hipMemcpyHostToDevice),
             "upload nuclei");
@@ -481,7 +604,7 @@ qmk_status provide_ao_sorted(qmk_ctx ctx, hipStream_t s, bool force = false) {
 // when that is current, else the value-only kernel into its own plane.
 // Returns the plane and its AO-row stride.
 qmk_status provide_ao_value(qmk_ctx ctx, hipStream_t s, const void** plane, int64_t* row_stride) {
-  qmk_status st = ensure_tables(ctx);
+  qmk_status st = ensure_tables(ctx, s);
   if (st != QMK_OK) return st;
   const int f32 = ctx->f32_storage() ? 1 : 0;
   const int64_t Pp = round_up(ctx->P(), kPointPad), Kp = round_up(ctx->ao_num, kAoPad);
@@ -552,7 +675,7 @@ bool solve4(double a[4][4], double b[4], double f[4]) {
 qmk_status ensure_cusp(qmk_ctx ctx, hipStream_t s) {
   const int64_t key[4] = {ctx->geom_version, ctx->coef_version, ctx->cusp_version, ctx->mode};
   if (std::equal(key, key + 4, ctx->cusp_key)) return QMK_OK;
-  qmk_status st = ensure_tables(ctx);
+  qmk_status st = ensure_tables(ctx, s);
   if (st != QMK_OK || (st = host_coef(ctx)) != QMK_OK) return st;
   const int64_t nn = ctx->nucl_num, K = ctx->ao_num, N = ctx->mo_num;
   const double* R = ctx->nucl.data();
@@ -583,7 +706,7 @@ qmk_status ensure_cusp(qmk_ctx ctx, hipStream_t s) {
   pa.s_ax = 1;
   pa.P = nn;
   AoOut o{ctx->d_cusp_ao.p, nn, 0, 1};
-  QMK_HIP(ctx, launch_ao_value(ctx->tab, pa, o, 0, s), "AO values at the nuclei");
+  QMK_HIP(ctx, launch_ao_value(ctx->tab_caller, pa, o, 0, s), "AO values at the nuclei");
   std::vector<double> chi(static_cast<size_t>(K * nn));
   QMK_HIP(ctx, hipMemcpyAsync(chi.data(), ctx->d_cusp_ao.p, chi.size() * 8, hipMemcpyDeviceToHost, s),
           "download AO values at the nuclei");
@@ -1000,6 +1123,7 @@ qmk_status qmk_set_basis(qmk_ctx ctx, int64_t shell_num, int64_t prim_num,
   ctx->prim_num = prim_num;
   ctx->ao_num = ao_num;
   ctx->has_basis = true;
+  ctx->row_of.clear();  // until the tables are built
   ctx->tables_dirty = true;
   ctx->coef_dirty = true;
   ++ctx->date;
@@ -1052,8 +1176,8 @@ qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* co
   *flag = 0;
   // the tables keep their shape when the nuclei move: their centres are
   // written in place, unless the tables are to be built anyway
-  const bool move = !ctx->tables_dirty;
-  if (move) ctx->tables_dirty = true;  // until the new centres are accepted
+  const bool move = !ctx->tables_dirty, ordered = ctx->ao_num >= kOrderRowsAo;
+  ctx->tables_dirty = true;  // until the new centres are accepted
   QMK_HIP(ctx, launch_take_params(coef, ctx->d_Craw_new.as<double>(), n, coord, nucl_num, host_xyz,
                                   move ? ctx->d_nuc.as<NucDev>() : nullptr, move ? ctx->nucl_dev : 0, flag, s),
           "take parameters");
@@ -1062,11 +1186,15 @@ qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* co
   const int64_t mo_before = ctx->mo_num;
   ctx->mo_num = mo_num;
   ctx->coef_dirty = true;
-  st = make_coef_copies(ctx, ctx->d_Craw_new.as<double>(), s);
-  if (st != QMK_OK) {
-    ctx->mo_num = mo_before;
-    ctx->coef_dirty = true;
-    return st;
+  if (!ordered) {
+    st = make_coef_copies(ctx, ctx->d_Craw_new.as<double>(), s);
+    if (st != QMK_OK) {
+      ctx->mo_num = mo_before;
+      ctx->coef_dirty = true;
+      return st;
+    }
+  } else {  // their rows' order follows the nuclei
+    QMK_HIP(ctx, hipStreamSynchronize(s), "take parameters");
   }
   for (int64_t i = 0; st == QMK_OK && i < n3; ++i)
     if (!std::isfinite(host_xyz[i])) st = fail(ctx, QMK_NONFINITE, "non-finite nuclear coordinate");
@@ -1077,7 +1205,7 @@ qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* co
     return st;
   }
   ctx->nucl.assign(host_xyz, host_xyz + n3);
-  if (move) ctx->tables_dirty = false;
+  ctx->tables_dirty = !move || (ordered && order_rows(ctx, ctx->nucl) != ctx->shell_row);
   std::swap(ctx->d_Craw.p, ctx->d_Craw_new.p);
   std::swap(ctx->d_Craw.bytes, ctx->d_Craw_new.bytes);
   ctx->craw_valid = true;
@@ -1411,12 +1539,12 @@ qmk_status qmk_get_ao_vgl(qmk_ctx ctx, void* out, int64_t size_max, int32_t dtyp
   if (size_max < need)
     return fail(ctx, QMK_SIZE, "size_max " + std::to_string(size_max) + " < " + std::to_string(need));
   DeviceGuard g(ctx->device);
-  st = ensure_tables(ctx);
-  if (st != QMK_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  st = ensure_tables(ctx, s);
+  if (st != QMK_OK) return st;
   AoOut o{out, 1, ctx->ao_num, 5 * ctx->ao_num};
   LaunchTimer lt(ctx, QMK_KERNEL_AO, s);
-  QMK_HIP(ctx, launch_ao_vgl(ctx->tab, point_args(ctx), o, dtype == QMK_F32, ctx->f32_storage(), s),
+  QMK_HIP(ctx, launch_ao_vgl(ctx->tab_caller, point_args(ctx), o, dtype == QMK_F32, ctx->f32_storage(), s),
           "AO kernel");
   return QMK_OK;
 }
@@ -1562,6 +1690,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
   const int f32 = prec == Prec::kF32 ? 1 : 0;
 
   // occupied MOs, compacted once per (occupations, coefficients, precision)
+  if ((st = ensure_tables(ctx, s)) != QMK_OK) return st;  // the order of its rows
   std::vector<double> key(occ, occ + N);
   if (key != ctx->occ_key || ctx->occ_coef_version != ctx->coef_version || ctx->occ_f32 != f32) {
     if ((st = host_coef(ctx)) != QMK_OK) return st;
@@ -1579,8 +1708,9 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
       w[j] = occ[rows[j]];
       for (int64_t k = 0; k < K; ++k) {
         const double c = ctx->C[rows[j] * K + k];
-        if (f32) ct32[k * Nop + j] = static_cast<float>(c);
-        else ct64[k * Nop + j] = c;
+        const int64_t row = ctx->row_of.empty() ? k : ctx->row_of[k];
+        if (f32) ct32[row * Nop + j] = static_cast<float>(c);
+        else ct64[row * Nop + j] = c;
       }
     }
     const size_t cb = static_cast<size_t>(Kp * Nop) * (f32 ? 4 : 8);
@@ -1640,7 +1770,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
     const TileCfg t = gemm_tile(prec, c);
     const int64_t slots = (ctx->n_occ + t.bn() - 1) / t.bn() * t.wgn;
     LaunchTimer lt(ctx, QMK_KERNEL_REDUCE, s);
-    return launch_reduce(RedJob{ctx->ws_den.as<double>(), slots, 1, P, 0, Pp, rho, 0}, RedJob{}, NucRedJob{}, s);
+    return launch_reduce(RedJob{ctx->ws_den.as<double>(), slots, 1, P, 0, Pp, rho, 0, nullptr}, RedJob{}, NucRedJob{}, s);
   };
   GemmProblem pb{GemmKind::kDensity, prec, 0, 0, P, ctx->n_occ, K};
   pb.nbatch = 1;
@@ -1786,7 +1916,7 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
                                      ctx->ws_nuc.as<double>(), s),
               "AO adjoint kernel");
     }
-    if (d_elec && elec_out != d_elec) red_elec = RedJob{elec_out, parts, P, 3, 3, P * 3, d_elec, 3};
+    if (d_elec && elec_out != d_elec) red_elec = RedJob{elec_out, parts, P, 3, 3, P * 3, d_elec, 3, nullptr};
     if (d_nucl)
       red_nuc = NucRedJob{ctx->ws_nuc.as<double>(), nw, ctx->nucl_dev, static_cast<int32_t>(ctx->nucl_num),
                           ctx->d_devof.as<int32_t>(), d_nucl};
@@ -1868,7 +1998,7 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
             : scr  ? launch_gemm_screened_adj(GemmKind::kDcoef, prec, cfg, ga, w32, s)
                 : launch_gemm_typed(GemmKind::kDcoef, prec, cfg, ga, w32, 0, s);
       }
-      red_coef = RedJob{ctx->ws_dc.as<double>(), 5 * nsplit, N, K, Kp, Np * Kp, d_coef, K};
+      red_coef = RedJob{ctx->ws_dc.as<double>(), 5 * nsplit, N, K, Kp, Np * Kp, d_coef, K, ctx->ao_of()};
       return e;
     };
     // (timed with the sum over its splits)

@@ -132,13 +132,14 @@ __global__ __launch_bounds__(256) void split_w_batch_kernel(const SplitJob* __re
 // The products' copies of C [N][K] (FP64): C [Np][Kp] and C^T [Kp][Np] in FP64
 // (MODE 0) or FP32 (1, 2), and in MODE 2 both split into bf16 hi / lo planes
 // (hi = bf16(c), lo = bf16(c - hi), the residual in FP64); zeros beyond N
-// and K.  Np and Kp are multiples of 32.  One 32 x 32 tile per workgroup,
+// and K; row k of the copies is the caller's AO ao_of[k].  Np and Kp are multiples of 32.  One 32 x 32 tile per workgroup,
 // transposed through LDS, so that every copy is stored in full lines.  Bound
 // by the latency of one pass: 800 AOs x 400 MOs 7 us, where the host loops and
 // 4 to 6 blocking uploads that this replaces took 3 ms.
 template <int MODE>
 __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restrict__ src, int64_t N, int64_t K,
-                                                          int64_t Np, int64_t Kp, CoefCopies o) {
+                                                          int64_t Np, int64_t Kp, const int32_t* __restrict__ ao_of,
+                                                          CoefCopies o) {
   typedef typename std::conditional<MODE == 0, double, float>::type T;
   __shared__ double tile[32][33];
   const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 32, n0 = static_cast<int64_t>(blockIdx.y) * 32;
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restri
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int64_t n = n0 + ty + 8 * q, k = k0 + tx;
-    const double v = n < N && k < K ? src[n * K + k] : 0.0;
+    const double v = n < N && k < K ? src[n * K + (ao_of ? ao_of[k] : k)] : 0.0;
     put(o, false, n * Kp + k, v);
     tile[ty + 8 * q][tx] = v;
   }
@@ -197,16 +198,16 @@ __global__ __launch_bounds__(256) void take_params_kernel(const double* __restri
 }  // namespace
 
 hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
-                              const CoefCopies& o, hipStream_t s) {
+                              const int32_t* ao_of, const CoefCopies& o, hipStream_t s) {
   if (N <= 0 || K <= 0) return hipSuccess;
   if (Np % 32 != 0 || Kp % 32 != 0 || Np < N || Kp < K || Np / 32 > 65535) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(Kp / 32), static_cast<unsigned>(Np / 32));
   if (mode == 0)
-    hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+    hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
   else if (mode == 1)
-    hipLaunchKernelGGL(coef_layout_kernel<1>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+    hipLaunchKernelGGL(coef_layout_kernel<1>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
   else
-    hipLaunchKernelGGL(coef_layout_kernel<2>, grid, dim3(256), 0, s, src, N, K, Np, Kp, o);
+    hipLaunchKernelGGL(coef_layout_kernel<2>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
   return hipGetLastError();
 }
 

@@ -93,6 +93,15 @@ struct qmk_ctx_s {
   bool tables_dirty = true;
   DevBuf d_nuc, d_shell, d_prim, d_aofac, d_group, d_devof;
   qmk::AoTables tab{};
+  // Rows of the context's own AO arrays (and of every copy of C and of Gbar):
+  // row_of[k] of the caller's AO k, and its inverse on the device; empty where
+  // the rows are in the caller's order.  tab_caller: the tables with the
+  // caller's rows (AO values for the caller, cusp tables).
+  std::vector<int64_t> shell_row;  // first row of every shell
+  std::vector<int32_t> row_of;
+  DevBuf d_ao_of, d_shell_caller, d_aofac_caller;
+  qmk::AoTables tab_caller{};
+  const int32_t* ao_of() const { return row_of.empty() ? nullptr : d_ao_of.as<int32_t>(); }
   int32_t n_groups = 0, nucl_dev = 0;
 
   // MO coefficient copies for the current mode
@@ -210,7 +219,7 @@ qmk_status bad_arg(qmk_ctx ctx, int k, const std::string& msg);
 qmk_status check_dev_arg(qmk_ctx ctx, int k, const void* p);
 qmk_status hip_fail(qmk_ctx ctx, hipError_t e, const char* what);
 bool valid_ctx(qmk_ctx ctx);
-qmk_status ensure_tables(qmk_ctx ctx);
+qmk_status ensure_tables(qmk_ctx ctx, hipStream_t s);
 // s: the stream that the copies are made on (complete on return).
 qmk_status ensure_coef(qmk_ctx ctx, hipStream_t s);
 qmk_status check_ready(qmk_ctx ctx, bool need_coef);

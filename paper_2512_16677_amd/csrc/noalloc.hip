@@ -95,10 +95,10 @@ extern "C" qmk_status qmk_get_mo_vgl_noalloc(qmk_ctx ctx, void* out, int64_t siz
                     std::to_string(need) + " bytes; the no-allocation scratch holds " +
                     std::to_string(kScratchBytes) + " (use qmk_get_mo_vgl, or fewer points per call)");
   DeviceGuard g(ctx->device);
-  if ((st = ensure_tables(ctx)) != QMK_OK) return st;  // tables are current: sets the cutoff only
+  hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  if ((st = ensure_tables(ctx, s)) != QMK_OK) return st;  // tables are current: sets the cutoff only
   void* ao = nullptr;
   QMK_HIP(ctx, scratch_address(ctx->device, &ao), "no-allocation scratch address");
-  hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
   const int64_t rows = 5 * K, total_rows = 5 * Kp;
   const int64_t n_pad = rows * (Pp - P) + (total_rows - rows) * Pp;

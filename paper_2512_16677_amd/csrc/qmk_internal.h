@@ -19,6 +19,14 @@ constexpr int kGroupMaxNuc = 128;
 // workgroups: at 120 an 800-AO system runs 7 workgroups per point block
 // instead of 1, which removes the tail of a grid of only ~2 workgroups per CU.
 constexpr int kGroupMaxAo = 120;
+// AOs from which the rows of the AO arrays follow reach and place instead of
+// the caller's order (see order_rows).  Screened passes in the caller's order
+// and in this one: 600 AOs 304 and 277 us (BF16x3 forward), 1200 AOs 815 and
+// 644 (FP64 forward), 643 and 558 (BF16x3 forward), 1650 AOs 2782 and 2211
+// (FP32 gradient).  Dense products do not gain from it, and every new set of
+// nuclei has to be checked for a new order (about 0.05 ms, 2 % of an
+// optimisation step of the 800-AO molecule), so the smaller ones go without.
+constexpr int64_t kOrderRowsAo = 1024;
 constexpr int kPointPad = 256;      // points are padded to a multiple of this
 constexpr int kAoPad = 128;         // AOs (K) padded to a multiple of this
 constexpr int kMoPad = 128;         // MOs (N) padded to a multiple of this
@@ -360,9 +368,10 @@ struct CoefCopies {
   void *c, *ct;
   void *c_hi, *c_lo, *ct_hi, *ct_lo;
 };
-// mode: 0 FP64, 1 FP32, 2 FP32 and bf16 planes.
+// mode: 0 FP64, 1 FP32, 2 FP32 and bf16 planes.  ao_of: the caller's AO of every
+// row k of the copies (NULL: k).
 hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
-                              const CoefCopies& o, hipStream_t s);
+                              const int32_t* ao_of, const CoefCopies& o, hipStream_t s);
 // n coefficients to coef_out, with *flag = 1 (device-visible, cleared by the
 // caller) if one is not finite; n_nucl nuclei to nucl_out and, unless nuc is
 // NULL, into the n_nuc entries of the nucleus table.
@@ -419,11 +428,13 @@ struct AdjJob {
   double* nuc_partial;
 };
 // out[r*ld_out + c] = sum_z ws[z*z_stride + r*ld_ws + c] for r < rows, c < cols
+// (column col[c] of out, where col is given)
 struct RedJob {
   const double* ws;
   int64_t nz, rows, cols, ld_ws, z_stride;
   double* out;
   int64_t ld_out;
+  const int32_t* col;
 };
 // out[3 A + i] = sum_w part[(w*nucl_dev + dev_of[A])*3 + i] over the n_waves
 // rows, or 0 for nuclei without shells (dev_of[A] < 0).
