@@ -326,8 +326,8 @@ GemmArgs gemm_job(qmk_batch b, size_t m, GemmKind kind, void* out, const void* w
       g.A2 = ao_lo;
       g.B = c->d_Cb_hi.p;
       g.B2 = c->d_Cb_lo.p;
-      g.sBl = 1;
-      g.sBj = mp.Kp;
+      g.sBl = mp.Np;  // slabs [Kp / 32][Np][32]
+      g.sBj = 32;
     } else {
       g.B = c->d_Ct.p;
       g.sBl = mp.Np;

@@ -841,10 +841,10 @@ GemmArgs gbar_args(Prec prec, const void* w, const void* w_lo, int64_t Nw, const
     // rows k, columns p (as below, so that Gbar is stored in full lines);
     // both operands are read along the reduction index n, as this kernel
     // needs
-    g.A = Ct_hi;  // C^T [k][n], split into bf16 hi + lo
+    g.A = Ct_hi;  // C^T in slabs [Np / 32][Kp][32], split into bf16 hi + lo
     g.A2 = Ct_lo;
-    g.sAi = Np;
-    g.sAl = 1;
+    g.sAi = 32;
+    g.sAl = Kp;
     g.B = w;  // W planes [Pp][5][Nw]
     g.B2 = w_lo;
     g.sBl = 1;
@@ -919,8 +919,8 @@ qmk_status get_mo_vgl_screened(qmk_ctx ctx, void* out, int32_t dtype, hipStream_
     ga.A2 = static_cast<const uint16_t*>(ctx->aos.p) + ctx->aos_Kp * 5 * Pp;
     ga.B = ctx->d_Cb_hi.p;
     ga.B2 = ctx->d_Cb_lo.p;
-    ga.sBl = 1;
-    ga.sBj = ctx->Kp;
+    ga.sBl = ctx->Np;  // slabs [Kp / 32][Np][32]
+    ga.sBj = 32;
   } else {
     ga.B = ctx->d_Ct.p;
     ga.sBl = ctx->Np;
@@ -1583,8 +1583,8 @@ qmk_status qmk_get_mo_vgl(qmk_ctx ctx, void* out, int64_t size_max, int32_t dtyp
     ga.A2 = static_cast<const uint16_t*>(ctx->ao.p) + ctx->ao_Kp * 5 * Pp;
     ga.B = ctx->d_Cb_hi.p;
     ga.B2 = ctx->d_Cb_lo.p;
-    ga.sBl = 1;
-    ga.sBj = ctx->Kp;
+    ga.sBl = ctx->Np;  // slabs [Kp / 32][Np][32]
+    ga.sBj = 32;
   } else {
     ga.B = ctx->d_Ct.p;
     ga.sBl = ctx->Np;

@@ -132,10 +132,16 @@ __global__ __launch_bounds__(256) void split_w_batch_kernel(const SplitJob* __re
 // The products' copies of C [N][K] (FP64): C [Np][Kp] and C^T [Kp][Np] in FP64
 // (MODE 0) or FP32 (1, 2), and in MODE 2 both split into bf16 hi / lo planes
 // (hi = bf16(c), lo = bf16(c - hi), the residual in FP64); zeros beyond N
-// and K; row k of the copies is the caller's AO ao_of[k].  Np and Kp are multiples of 32.  One 32 x 32 tile per workgroup,
-// transposed through LDS, so that every copy is stored in full lines.  Bound
-// by the latency of one pass: 800 AOs x 400 MOs 7 us, where the host loops and
-// 4 to 6 blocking uploads that this replaces took 3 ms.
+// and K; row k of the copies is the caller's AO ao_of[k].  Np and Kp are
+// multiples of 32.  The planes are in slabs of 32 reduction indices, [Kp / 32]
+// [Np][32] of C and [Np / 32][Kp][32] of C^T: a K step of a product's tile is
+// one run of memory (with rows of Kp or Np, 64 bytes of every row: 7500-AO
+// screened forward pass 2.53 ms, 2.43 in slabs; 800-AO gradient with a step of
+// the parameters 3.23 and 3.16 ms).
+// One 32 x 32 tile per workgroup, transposed through LDS, so that every copy is
+// stored in full lines.  Bound by the latency of one pass: 800 AOs x 400 MOs
+// 7 us, where the host loops and 4 to 6 blocking uploads that this replaces
+// took 3 ms.
 template <int MODE>
 __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restrict__ src, int64_t N, int64_t K,
                                                           int64_t Np, int64_t Kp, const int32_t* __restrict__ ao_of,
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restri
   __shared__ double tile[32][33];
   const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 32, n0 = static_cast<int64_t>(blockIdx.y) * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  auto put = [](const CoefCopies& c, bool transposed, int64_t at, double v) {
+  auto put = [](const CoefCopies& c, bool transposed, int64_t at, int64_t slab_at, double v) {
     static_cast<T*>(transposed ? c.ct : c.c)[at] = static_cast<T>(v);
     if constexpr (MODE == 2) {
       float f = static_cast<float>(v);
@@ -153,20 +159,23 @@ __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restri
       const __bf16 h = static_cast<__bf16>(f);
       float r = static_cast<float>(v - static_cast<double>(static_cast<float>(h)));
       asm volatile("" : "+v"(r));
-      static_cast<__bf16*>(transposed ? c.ct_hi : c.c_hi)[at] = h;
-      static_cast<__bf16*>(transposed ? c.ct_lo : c.c_lo)[at] = static_cast<__bf16>(r);
+      static_cast<__bf16*>(transposed ? c.ct_hi : c.c_hi)[slab_at] = h;
+      static_cast<__bf16*>(transposed ? c.ct_lo : c.c_lo)[slab_at] = static_cast<__bf16>(r);
     }
   };
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int64_t n = n0 + ty + 8 * q, k = k0 + tx;
     const double v = n < N && k < K ? src[n * K + (ao_of ? ao_of[k] : k)] : 0.0;
-    put(o, false, n * Kp + k, v);
+    put(o, false, n * Kp + k, k0 * Np + n * 32 + tx, v);
     tile[ty + 8 * q][tx] = v;
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) put(o, true, (k0 + ty + 8 * q) * Np + n0 + tx, tile[tx][ty + 8 * q]);
+  for (int q = 0; q < 4; ++q) {
+    const int64_t k = k0 + ty + 8 * q;
+    put(o, true, k * Np + n0 + tx, n0 * Kp + k * 32 + tx, tile[tx][ty + 8 * q]);
+  }
 }
 
 // dst = src, with *flag = 1 where a value is not finite; the first workgroup

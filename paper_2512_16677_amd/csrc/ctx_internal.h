@@ -114,8 +114,8 @@ struct qmk_ctx_s {
   void* pin = nullptr;       // pinned host memory that a kernel writes: flag, nuclei
   size_t pin_bytes = 0;
   DevBuf d_Ct, d_C;          // FP64 or FP32 copies: C^T [Kp][Np], C [Np][Kp]
-  DevBuf d_Cb_hi, d_Cb_lo;   // BF16x3: C [Np][Kp] split into bf16 hi / lo
-  DevBuf d_Ctb_hi, d_Ctb_lo; // BF16x3: C^T [Kp][Np] split
+  DevBuf d_Cb_hi, d_Cb_lo;   // BF16x3: C in slabs [Kp / 32][Np][32], split into bf16 hi / lo
+  DevBuf d_Ctb_hi, d_Ctb_lo; // BF16x3: C^T in slabs [Np / 32][Kp][32], split
 
   // AO array [Kp][5][Pp] (double or float), valid at ao_date
   DevBuf ao;

@@ -133,8 +133,8 @@ extern "C" qmk_status qmk_get_mo_vgl_noalloc(qmk_ctx ctx, void* out, int64_t siz
     ga.A2 = static_cast<const uint16_t*>(ao) + total_rows * Pp;
     ga.B = ctx->d_Cb_hi.p;
     ga.B2 = ctx->d_Cb_lo.p;
-    ga.sBl = 1;
-    ga.sBj = ctx->Kp;
+    ga.sBl = ctx->Np;  // slabs [Kp / 32][Np][32]
+    ga.sBj = 32;
   } else {
     ga.B = ctx->d_Ct.p;
     ga.sBl = ctx->Np;

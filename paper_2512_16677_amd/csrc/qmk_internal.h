@@ -167,7 +167,9 @@ struct GemmArgs {
   int64_t sDi, sDj, oDz;
   int64_t M, N, L, Lchunk;
   int32_t nsplit, nbatch;   // gridDim.y = nbatch * nsplit
-  // BF16x3 kernel only: second (lo) plane of a pre-split operand.
+  // BF16x3 kernel only: second (lo) plane of a pre-split operand.  There the
+  // strides along l of a K-major operand hold from one K step of 32 to the
+  // next (32 elements each), and the 32 of a step are contiguous.
   const void* A2;
   const void* B2;
   // Workgroup -> tile order of the grid launch.  0: the N tiles of one M tile
