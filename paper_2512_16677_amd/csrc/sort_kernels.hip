@@ -3,9 +3,9 @@
 // sparsity is usable only if the points of a tile are close in space: points
 // are sorted by their nearest nucleus, so that a 64-point block sees the AOs
 // of one neighbourhood.  The sort is a stable counting sort of the points by
-// nearest nucleus (keys 0 .. n_nuc-1), so the order -- and with it every sum
+// nearest nucleus and, within it, by distance (see key_of), so the order -- and with it every sum
 // over sorted points -- is the same on every run:
-//   1. nearest nucleus of every point, and per block of kSortBlock points the
+//   1. nearest nucleus of every point, and per block of points the
 //      count of each key (LDS histogram), stored as hist[key][block];
 //   2. exclusive scan of hist in (key, block) order: each key's blocks in
 //      order, one wave per key, then the keys' totals in order;
@@ -17,23 +17,45 @@
 namespace qmk {
 namespace {
 
-constexpr int kSortBlock = 1024;                // points per histogram block (4 per thread)
 constexpr int kSortMaxKeys = kSortMaxNuclei;  // LDS histogram of one block
 
+// Keys per nucleus: its points in kRings rings, near to far for one nucleus and
+// far to near for the next, so that the far points of neighbours, which see
+// more of the AOs around, share tiles.  7500 AOs, 63,000 points, B = 24: a
+// 128-point tile visits 0.097 of its K steps, 0.104 with one key per nucleus
+// (BF16x3 product 1.95 and 2.06 ms).  One key where four would not fit the tables.
+constexpr int kRings = 4;
+int rings(int64_t P, int64_t n_nuc) {
+  return n_nuc * kRings <= kSortMaxKeys && (P + 1023) / 1024 * n_nuc * kRings <= (int64_t(1) << 22) ? kRings : 1;
+}
+__device__ __forceinline__ int32_t key_of(int32_t nucleus, double u, int rings) {
+  if (rings == 1) return nucleus;
+  const int r = (u > 0.75 * 0.75) + (u > 1.25 * 1.25) + (u > 1.75 * 1.75);
+  return nucleus * kRings + ((nucleus & 1) ? kRings - 1 - r : r);
+}
+
+// Points per histogram block: 256, which puts a wave of the nearest-nucleus
+// pass on every SIMD at 63,000 points (300 nuclei: that pass 119 us with 1024
+// points in a block, 38 with 256, the scatter 43 and 15), unless the table of
+// all blocks' counts would then exceed 16 MB.
+int sort_block(int64_t P, int64_t n_keys) { return (P + 255) / 256 * n_keys <= (int64_t(1) << 22) ? 256 : 1024; }
+
+// Bound by the chain of one point's comparisons.
 __global__ __launch_bounds__(256) void nearest_nucleus_kernel(PointArgs pts, const double* __restrict__ nuc,
-                                                              int64_t n_nuc, int64_t n_blocks,
-                                                              int32_t* __restrict__ key,
+                                                              int64_t n_nuc, int64_t n_keys, int64_t n_blocks,
+                                                              int block, int rings, int32_t* __restrict__ key,
                                                               int32_t* __restrict__ hist) {
-  __shared__ int32_t h[kSortMaxKeys];
-  for (int64_t i = threadIdx.x; i < n_nuc; i += blockDim.x) h[i] = 0;
+  extern __shared__ int32_t h[];
+  for (int64_t i = threadIdx.x; i < n_keys; i += blockDim.x) h[i] = 0;
   __syncthreads();
-  for (int r = 0; r < kSortBlock / 256; ++r) {
-    const int64_t p = static_cast<int64_t>(blockIdx.x) * kSortBlock + r * 256 + threadIdx.x;
+  for (int r = 0; r < block / 256; ++r) {
+    const int64_t p = static_cast<int64_t>(blockIdx.x) * block + r * 256 + threadIdx.x;
     if (p >= pts.P) break;
     const double x = pts.coord[p * pts.s_pt], y = pts.coord[p * pts.s_pt + pts.s_ax],
                  z = pts.coord[p * pts.s_pt + 2 * pts.s_ax];
     double best = INFINITY;
     int32_t arg = 0;
+#pragma unroll 4
     for (int64_t a = 0; a < n_nuc; ++a) {
       const double u = dist2(x - nuc[3 * a], y - nuc[3 * a + 1], z - nuc[3 * a + 2]);
       if (u < best) {
@@ -41,20 +63,21 @@ __global__ __launch_bounds__(256) void nearest_nucleus_kernel(PointArgs pts, con
         arg = static_cast<int32_t>(a);
       }
     }
-    key[p] = arg;
-    atomicAdd(&h[arg], 1);
+    const int32_t k = key_of(arg, best, rings);
+    key[p] = k;
+    atomicAdd(&h[k], 1);
   }
   __syncthreads();
-  for (int64_t i = threadIdx.x; i < n_nuc; i += blockDim.x) hist[i * n_blocks + blockIdx.x] = h[i];
+  for (int64_t i = threadIdx.x; i < n_keys; i += blockDim.x) hist[i * n_blocks + blockIdx.x] = h[i];
 }
 
 // One wave per key: exclusive scan of the key's block counts in place; the
 // key's total to tot[key].
-__global__ __launch_bounds__(256) void scan_blocks_kernel(int32_t* __restrict__ hist, int64_t n_nuc,
+__global__ __launch_bounds__(256) void scan_blocks_kernel(int32_t* __restrict__ hist, int64_t n_keys,
                                                           int64_t n_blocks, int32_t* __restrict__ tot) {
   const int64_t k = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (k >= n_nuc) return;
+  if (k >= n_keys) return;
   int32_t* row = hist + k * n_blocks;
   int32_t carry = 0;
   for (int64_t b0 = 0; b0 < n_blocks; b0 += 64) {
@@ -72,15 +95,15 @@ __global__ __launch_bounds__(256) void scan_blocks_kernel(int32_t* __restrict__ 
 }
 
 // One workgroup: exclusive scan of the keys' totals in place.
-__global__ __launch_bounds__(1024) void scan_keys_kernel(int32_t* __restrict__ tot, int64_t n_nuc) {
+__global__ __launch_bounds__(1024) void scan_keys_kernel(int32_t* __restrict__ tot, int64_t n_keys) {
   __shared__ int32_t wsum[16];
   __shared__ int32_t s_carry;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (threadIdx.x == 0) s_carry = 0;
   __syncthreads();
-  for (int64_t k0 = 0; k0 < n_nuc; k0 += 1024) {
+  for (int64_t k0 = 0; k0 < n_keys; k0 += 1024) {
     const int64_t k = k0 + threadIdx.x;
-    const int32_t v = k < n_nuc ? tot[k] : 0;
+    const int32_t v = k < n_keys ? tot[k] : 0;
     int32_t incl = v;
     for (int off = 1; off < 64; off <<= 1) {
       const int32_t o = __shfl_up(incl, off, 64);
@@ -90,7 +113,7 @@ __global__ __launch_bounds__(1024) void scan_keys_kernel(int32_t* __restrict__ t
     __syncthreads();
     int32_t before = s_carry;
     for (int i = 0; i < w; ++i) before += wsum[i];
-    if (k < n_nuc) tot[k] = before + incl - v;
+    if (k < n_keys) tot[k] = before + incl - v;
     __syncthreads();
     if (threadIdx.x == 0) {
       int32_t t = 0;
@@ -101,18 +124,18 @@ __global__ __launch_bounds__(1024) void scan_keys_kernel(int32_t* __restrict__ t
   }
 }
 
-// One wave per block of kSortBlock points, walking them 64 at a time in
-// order: stable positions from the per-key running offsets in LDS.
-__global__ __launch_bounds__(64) void scatter_kernel(const int32_t* __restrict__ key, int64_t P, int64_t n_nuc,
-                                                     int64_t n_blocks, const int32_t* __restrict__ hist,
+// One wave per block of points, walking them 64 at a time in order: stable
+// positions from the per-key running offsets in LDS.
+__global__ __launch_bounds__(64) void scatter_kernel(const int32_t* __restrict__ key, int64_t P, int64_t n_keys,
+                                                     int64_t n_blocks, int block, const int32_t* __restrict__ hist,
                                                      const int32_t* __restrict__ tot, int32_t* __restrict__ perm) {
-  __shared__ int32_t next[kSortMaxKeys];
+  extern __shared__ int32_t next[];
   const int lane = threadIdx.x;
   const int64_t blk = blockIdx.x;
-  for (int64_t i = lane; i < n_nuc; i += 64) next[i] = tot[i] + hist[i * n_blocks + blk];
+  for (int64_t i = lane; i < n_keys; i += 64) next[i] = tot[i] + hist[i * n_blocks + blk];
   __syncthreads();
-  for (int r = 0; r < kSortBlock / 64; ++r) {
-    const int64_t p = blk * kSortBlock + r * 64 + lane;
+  for (int r = 0; r < block / 64; ++r) {
+    const int64_t p = blk * block + r * 64 + lane;
     const bool in = p < P;
     const int32_t k = in ? key[p] : -1;
     // rank among the earlier lanes with the same key
@@ -164,25 +187,31 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s) {
 }
 
 size_t sort_scratch_bytes(int64_t P, int64_t n_nuc) {
-  const int64_t n_blocks = (P + kSortBlock - 1) / kSortBlock;
-  return static_cast<size_t>((n_nuc * n_blocks + n_nuc) * 4);
+  const int64_t n_keys = n_nuc * rings(P, n_nuc);
+  const int block = sort_block(P, n_keys);
+  const int64_t n_blocks = (P + block - 1) / block;
+  return static_cast<size_t>((n_keys * n_blocks + n_keys) * 4);
 }
 
 hipError_t launch_sort_points(const PointArgs& pts, const double* nuc_xyz, int64_t n_nuc, int32_t* key,
                               int32_t* perm, void* scratch, size_t scratch_bytes, hipStream_t s) {
   if (pts.P <= 0) return hipSuccess;
   if (n_nuc < 1 || n_nuc > kSortMaxKeys || pts.P > 0x7fffffffLL) return hipErrorInvalidValue;
-  const int64_t n_blocks = (pts.P + kSortBlock - 1) / kSortBlock;
+  const int nr = rings(pts.P, n_nuc);
+  const int64_t n_keys = n_nuc * nr;
+  const int block = sort_block(pts.P, n_keys);
+  const int64_t n_blocks = (pts.P + block - 1) / block;
+  const size_t lds = static_cast<size_t>(n_keys) * 4;
   if (scratch_bytes < sort_scratch_bytes(pts.P, n_nuc)) return hipErrorInvalidValue;
   int32_t* hist = static_cast<int32_t*>(scratch);
-  int32_t* tot = hist + n_nuc * n_blocks;
-  hipLaunchKernelGGL(nearest_nucleus_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(256), 0, s, pts, nuc_xyz,
-                     n_nuc, n_blocks, key, hist);
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(static_cast<unsigned>((n_nuc + 3) / 4)), dim3(256), 0, s, hist, n_nuc,
+  int32_t* tot = hist + n_keys * n_blocks;
+  hipLaunchKernelGGL(nearest_nucleus_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(256), lds, s, pts, nuc_xyz,
+                     n_nuc, n_keys, n_blocks, block, nr, key, hist);
+  hipLaunchKernelGGL(scan_blocks_kernel, dim3(static_cast<unsigned>((n_keys + 3) / 4)), dim3(256), 0, s, hist, n_keys,
                      n_blocks, tot);
-  hipLaunchKernelGGL(scan_keys_kernel, dim3(1), dim3(1024), 0, s, tot, n_nuc);
-  hipLaunchKernelGGL(scatter_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(64), 0, s, key, pts.P, n_nuc,
-                     n_blocks, hist, tot, perm);
+  hipLaunchKernelGGL(scan_keys_kernel, dim3(1), dim3(1024), 0, s, tot, n_keys);
+  hipLaunchKernelGGL(scatter_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(64), lds, s, key, pts.P, n_keys,
+                     n_blocks, block, hist, tot, perm);
   return hipGetLastError();
 }
 
