@@ -208,6 +208,18 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
   OutT* const obase = static_cast<OutT*>(out.out) + p * out.sP +
                       ((kPairs && (threadIdx.x & 1)) ? out.plane - 1 : 0);
   const double T = t.T;
+  // SCR = 2: the bitmap rows of the wave's block, one word per lane, so that
+  // the shells' tests wait for no loads (7500 AOs, 63,000 points: 377 us with
+  // two loads per shell and chunk, 320 so); beyond 64 words (32,768 AOs) they load.
+  uint32_t act_now = 0, act_was = 0;
+  const int64_t blk = (static_cast<int64_t>(bx) * blockDim.x + (threadIdx.x & ~63)) >> 6;
+  if constexpr (SCR == 2) {
+    const int lane = threadIdx.x & 63;
+    if (lane < out.act_words) {
+      act_now = out.act[blk * out.act_words + lane];
+      act_was = out.act_prev[blk * out.act_words + lane];
+    }
+  }
 
   for (int a = 0; a < nn; ++a) {
     const NucDev nu = s_nuc[a];
@@ -240,13 +252,20 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
       const ShellDev sh = s_shell[s];
       if constexpr (SCR == 2) {
         // the wave's block: chunks of this shell active now, or before
-        const int64_t blk = (static_cast<int64_t>(bx) * blockDim.x + (threadIdx.x & ~63)) >> 6;
-        const int c0 = sh.ao_off / kSparseChunk;
-        const int c1 = (sh.ao_off + (sh.l + 1) * (sh.l + 2) / 2 - 1) / kSparseChunk;
+        const int c0 = __builtin_amdgcn_readfirstlane(sh.ao_off / kSparseChunk);
+        const int c1 = __builtin_amdgcn_readfirstlane((sh.ao_off + (sh.l + 1) * (sh.l + 2) / 2 - 1) / kSparseChunk);
         bool now = false, was = false;
         for (int c = c0; c <= c1; ++c) {
-          now = now || ((out.act[blk * out.act_words + (c >> 5)] >> (c & 31)) & 1u);
-          was = was || ((out.act_prev[blk * out.act_words + (c >> 5)] >> (c & 31)) & 1u);
+          uint32_t wn, ww;
+          if (out.act_words <= 64) {
+            wn = __builtin_amdgcn_readlane(act_now, c >> 5);
+            ww = __builtin_amdgcn_readlane(act_was, c >> 5);
+          } else {
+            wn = out.act[blk * out.act_words + (c >> 5)];
+            ww = out.act_prev[blk * out.act_words + (c >> 5)];
+          }
+          now = now || ((wn >> (c & 31)) & 1u);
+          was = was || ((ww >> (c & 31)) & 1u);
         }
         if (!now || !any_near) {
           if (now || was)
