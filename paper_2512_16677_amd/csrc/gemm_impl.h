@@ -190,8 +190,36 @@ __device__ __forceinline__ void dma_loop(T* stages, const T* At, const T* Bt, in
 #pragma unroll
     for (int q = 0; q < IPW; ++q) dma_b128(gp[q] + (isa[q] ? oa : ob), sb + ldso[q]);
   };
-  // fragments of sub-step kk + 1 are read before the products of kk
-  auto compute = [&](const T* sa) {
+  // Loads in parts, one per sub-step: a wave whose load instructions queue up
+  // behind one another issues no products meanwhile.  FP64 always (75,000
+  // points x 800 AOs x 400 MOs: forward product 3.57 -> 3.53 ms, Gbar 3.51 ->
+  // 3.44 ms; density of 785,603 points 7.16 -> 7.00 ms); FP32 with the eight
+  // sub-steps of BK = 32 (549 -> 541 us at 51,000 points), while with four it
+  // lost 5 % to the branches.
+  constexpr bool kParts = SZ == 8 || BK == 32;
+  constexpr int PER = (IPW + BK / 4 - 1) / (BK / 4);
+  // part kk of the loads of a step (offsets oa, ob) into the stage at sb
+  auto issue_part = [&](int kk, uint32_t sb, int64_t oa, int64_t ob) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int q = kk * PER + u;
+      if (q < IPW) dma_b128(gp[q] + (isa[q] ? oa : ob), sb + ldso[q]);
+    }
+  };
+  // fragments of sub-step kk + 1 are read before the products of kk, and the
+  // loads of step kt (when `more`) are issued a part per sub-step
+  auto compute = [&](const T* sa, bool more, int nslot, int64_t kt) {
+    int64_t oa = 0, ob = 0;
+    uint32_t nb = 0;
+    if constexpr (kParts) {
+      if (more) {
+        const int64_t t = __builtin_amdgcn_readfirstlane(static_cast<int>(kt));
+        oa = t * stepA;
+        ob = t * stepB;
+        nb = lds0 + static_cast<uint32_t>(nslot * STAGE * SZ);
+      }
+      asm("" : "+s"(oa), "+s"(ob));
+    }
     const T* sb = sa + BM * BK;
     const int ci = lane & 15, kq = lane >> 4;
     T fa[2][TM], fb[2][TN];
@@ -210,6 +238,9 @@ __device__ __forceinline__ void dma_loop(T* stages, const T* At, const T* Bt, in
 #pragma unroll
     for (int kk = 0; kk < BK / 4; ++kk) {
       if (kk + 1 < BK / 4) rd(kk + 1, (kk + 1) & 1);
+      if constexpr (kParts) {
+        if (more) issue_part(kk, nb, oa, ob);
+      }
 #pragma unroll
       for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -248,11 +279,12 @@ __device__ __forceinline__ void dma_loop(T* stages, const T* At, const T* Bt, in
     // step cur has landed; the stage read in the step before it is free
     dma_sync();
     int64_t after = end;
-    if (nxt < end && nxt != part) {
-      issue(slot ^ 1, nxt);
+    const bool more = nxt < end && nxt != part;
+    if (more) {
+      if constexpr (!kParts) issue(slot ^ 1, nxt);
       after = next(nxt);
     }
-    compute(stages + slot * STAGE);
+    compute(stages + slot * STAGE, more, slot ^ 1, nxt);
     cur = nxt;
     nxt = after;
     slot ^= 1;
@@ -263,7 +295,7 @@ __device__ __forceinline__ void dma_loop(T* stages, const T* At, const T* Bt, in
     T* st = stages + slot * STAGE;
     stage_tail(st, cur);
     __syncthreads();
-    compute(st);
+    compute(st, false, 0, 0);
   }
 }
 
