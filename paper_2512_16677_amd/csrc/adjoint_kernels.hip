@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256) void reduce_nuc_batch_kernel(const NucRedJob* 
                                                                int n_jobs) {
   __shared__ double red[256];
   const int64_t e = blockIdx.x;
-  const int jb = find_job(prefix, n_jobs, e);
+  const int jb = find_job(prefix, n_jobs, e, e);
   reduce_nuc(jobs[jb], e - prefix[jb], red);
 }
 
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const RedJob* __restr
                                                            int64_t total) {
   __shared__ double sm[4][64];
   const int64_t e = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
-  const int jb = find_job(prefix, n_jobs, min(e, total - 1));
+  const int jb = find_job(prefix, n_jobs, static_cast<int64_t>(blockIdx.x) * 64, min(e, total - 1));
   reduce_64(jobs[jb], e - prefix[jb], e < total, sm);
 }
 

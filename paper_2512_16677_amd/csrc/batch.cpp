@@ -639,10 +639,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
                            static_cast<double*>(b->ws_nuc.p) + mp.nuc_off};
       if (b->prec == Prec::kBF16P) {
         uint16_t* hi = b->wsplit.as<uint16_t>() + mp.w_off;
-        const size_t esz_w = w32 ? 4 : 8;
-        // vector loads need every group of eight weights to start 16-byte aligned
-        const int vec = reinterpret_cast<uintptr_t>(ws[i]) % 16 == 0 && (mp.N * esz_w) % 16 == 0;
-        split.push_back(SplitJob{ws[i], mp.P, mp.N, mp.Pp, mp.Nw, vec, hi, hi + mp.Pp * 5 * mp.Nw});
+        split.push_back(SplitJob{ws[i], mp.P, mp.N, mp.Pp, mp.Nw, hi, hi + mp.Pp * 5 * mp.Nw});
         const int64_t nj = mp.Pp * 5 * (mp.Nw / 8);
         if (nj > 0xffffffffLL) return bfail(b, QMK_SIZE, "context " + std::to_string(i) + ": W too large to split");
         split_prefix.push_back(split_prefix.back() + nj);

@@ -473,14 +473,20 @@ hipError_t launch_gemm_bf16p_persist(GemmKind kind, int cfg, const GemmArgs* job
 // kernel's loaders for tile cfg.
 bool gemm_bf16p_args_ok(int cfg, const GemmArgs& g);
 // Largest j with prefix[j] <= e (prefix[0] = 0, increasing): the job of
-// flat element e in the batched element-wise kernels.
-__device__ __forceinline__ int find_job(const int64_t* prefix, int n_jobs, int64_t e) {
+// flat element e in the batched element-wise kernels.  first: an element not
+// after e, the same for the whole wave, near it; the search is then scalar.
+__device__ __forceinline__ int find_job(const int64_t* prefix, int n_jobs, int64_t first, int64_t e) {
   int lo = 0, hi = n_jobs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= e) lo = mid; else hi = mid - 1;
+    if (prefix[mid] <= first) lo = mid; else hi = mid - 1;
   }
+  while (lo + 1 < n_jobs && prefix[lo + 1] <= e) ++lo;
   return lo;
+}
+// First element of the wave of a one-element-per-thread launch.
+__device__ __forceinline__ int64_t wave_first() {
+  return static_cast<int64_t>(blockIdx.x) * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
 }
 // Batched W split (batch executor): job j covers elements prefix[j] ..
 // prefix[j+1]-1 of a flat range, one per eight weights of its planes (fewer
@@ -488,7 +494,6 @@ __device__ __forceinline__ int find_job(const int64_t* prefix, int n_jobs, int64
 struct SplitJob {
   const void* w;
   int64_t P, N, Pp, Nw;
-  int32_t vec;
   void* hi;
   void* lo;
 };
