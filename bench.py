@@ -725,9 +725,9 @@ def main_jastrow(a):
     tm = ctx.timing()
     ctx.close()
     W, ne, nn = s.walk_num, s.elec_num, s.nucl_num
-    # the product: rows (m = 1..nord/2, nucleus), splits k = 0..nord-2
-    M, nsplit = (nord // 2) * nn, nord - 1
-    flops = 2.0 * W * nsplit * M * ne * ne
+    # the product: the (k, m) with k, m >= 1 that some term uses, per nucleus
+    pairs = {(k, (p - k - l) // 2) for p, k, l in oracle.een_terms(nord) if k >= 1 and p - k - l >= 2}
+    flops = 2.0 * W * len(pairs) * nn * ne * ne
     p_ms = tm["jastrow_p"]["ms"] / tm["jastrow_p"]["launches"]
     tf = flops / (p_ms * 1e-3) / 1e12
     line = {"metric": "three-body Jastrow electron-evals/s", "value": W * ne / (ms * 1e-3),
@@ -738,7 +738,7 @@ def main_jastrow(a):
                                    f"J_een order {nord}, kappa {kappa}"},
             "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAKS["fp64_TFLOPs"], "unit": "TFLOP/s",
                          "frac": tf / PEAKS["fp64_TFLOPs"], "traffic": None,
-                         "kernel": "gemm_kernel EPI 5 (P product, fused weights)"},
+                         "kernel": "een_product_kernel (P product, fused weights)"},
             "kernels_ms_per_step": {k: tm[k]["ms"] / a.steps for k in ("jastrow", "jastrow_p")}}
     if not a.no_cpu_baseline:
         n = max(1, min(a.cpu_walkers, W))
