@@ -91,6 +91,24 @@ struct TableSet {
 
 }  // namespace
 
+// The tiles of one batched product: t[0], and t[1] (-1: none) for the
+// molecules that it suits better (tile_of).  ratio: the time of t[1] per unit
+// of padded work over that of t[0], in 64ths.  One int in the tile table; a
+// plain tile number is that tile alone.
+struct BatchTiles {
+  int t[2] = {-1, -1};
+  int ratio = 64;
+  int code() const { return t[1] < 0 ? t[0] : t[0] | (t[1] + 1) << 8 | ratio << 16; }
+  static BatchTiles of(int code) {
+    BatchTiles b;
+    if (code < 0) return b;
+    b.t[0] = code & 255;
+    b.t[1] = ((code >> 8) & 255) - 1;
+    if (b.t[1] >= 0) b.ratio = code >> 16;
+    return b;
+  }
+};
+
 struct qmk_batch_s {
   uint32_t magic = kBatchMagic;
   int device = 0;
@@ -110,9 +128,10 @@ struct qmk_batch_s {
 
   // work lists (fixed per plan) and job tables (rewritten every run)
   std::vector<WorkItem> ao_items;
-  int tile[3] = {-1, -1, -1};
+  BatchTiles tile[3];
   int tile_w32 = -1, tile_o32 = -1;
-  std::vector<WorkItem> g_items[3];
+  std::vector<WorkItem> g_items[3];  // of tile.t[0], then of tile.t[1]
+  size_t g_first[3] = {0, 0, 0};     // items of tile.t[0]
   std::vector<GemmArgs> g_jobs[3];  // host copies of the product job tables
   DevBuf d_ao_items, d_g_items[3], d_tables;
   TabPtr d_ao_jobs, d_adj_jobs, d_g_jobs[3], d_red_jobs, d_red_prefix, d_nred_jobs,
@@ -158,6 +177,26 @@ void drop_graph(qmk_batch b) {
   b->graph_adj = b->graph_o32 = b->graph_w32 = -1;
 }
 
+// Work of one product of a molecule with tile `cfg`, in outputs times reduction
+// length: whole tiles, and about 128 reduction indices' worth per tile for its
+// first loads and its stores.
+double tile_work(qmk_batch b, GemmKind kind, const MolPlan& mp, int cfg) {
+  const TileCfg t = gemm_tile(b->prec, cfg);
+  const int64_t M = kind == GemmKind::kForward ? mp.P : (kind == GemmKind::kGbar ? mp.K : mp.N);
+  const int64_t N = kind == GemmKind::kForward ? mp.N : (kind == GemmKind::kGbar ? mp.P : mp.K);
+  const int64_t L = kind == GemmKind::kForward ? mp.K : (kind == GemmKind::kGbar ? mp.N : mp.P);
+  const int64_t splits = kind == GemmKind::kDcoef ? mp.nsplit : 1;
+  return 5.0 * static_cast<double>(round_up(M, t.bm())) * static_cast<double>(round_up(N, t.bn())) *
+         static_cast<double>(L + 128 * splits);
+}
+
+// The tile of a pair with the less expected time for a molecule.
+int tile_of(qmk_batch b, GemmKind kind, const MolPlan& mp, const BatchTiles& pair) {
+  if (pair.t[1] < 0) return pair.t[0];
+  return 64.0 * tile_work(b, kind, mp, pair.t[0]) <= pair.ratio * tile_work(b, kind, mp, pair.t[1]) ? pair.t[0]
+                                                                                                   : pair.t[1];
+}
+
 // Work list of one product for tile `cfg`: (molecule, M tile, N tile, z),
 // longest reduction first.  Consecutive workgroups land on the eight XCDs in
 // turn, so entry i belongs to XCD i % 8 (the grid is a multiple of eight where
@@ -170,7 +209,7 @@ void drop_graph(qmk_batch b) {
 // of 75 to 560 AOs in FP64: W^T ao product 4.10 ms with the tiles dealt out one by
 // one, 3.53 so; W C product 3.57 and 3.41 ms, forward 3.07 and 3.00 ms; 48
 // molecules in BF16x3: 1.78 and 1.39, 1.58 and 1.49, 1.33 and 1.27 ms.
-std::vector<WorkItem> gemm_items(qmk_batch b, GemmKind kind, int cfg) {
+std::vector<WorkItem> gemm_items(qmk_batch b, GemmKind kind, int cfg, const BatchTiles* pair = nullptr) {
   constexpr int kXcds = 8;
   const TileCfg t = gemm_tile(b->prec, cfg);
   struct Group {
@@ -187,6 +226,7 @@ std::vector<WorkItem> gemm_items(qmk_batch b, GemmKind kind, int cfg) {
   };
   for (size_t k = 0; k < b->plan.size(); ++k) {
     const MolPlan& mp = b->plan[k];
+    if (pair && tile_of(b, kind, mp, *pair) != cfg) continue;
     const int32_t m = static_cast<int32_t>(k);
     int64_t nM, nN;
     tiles(mp, &nM, &nN);
@@ -228,7 +268,7 @@ std::vector<WorkItem> gemm_items(qmk_batch b, GemmKind kind, int cfg) {
 qmk_status make_plan(qmk_batch b, hipStream_t s) {
   drop_graph(b);
   b->plan.clear();
-  b->tile[0] = b->tile[1] = b->tile[2] = -1;
+  for (BatchTiles& t : b->tile) t = BatchTiles();
   size_t ao = 0, dc = 0, nuc = 0, elec = 0, dis = 0, wsp = 0, wpd = 0;
   const bool planes = b->prec == Prec::kBF16P;
   b->max_smem = 0;
@@ -395,63 +435,129 @@ std::string batch_key(qmk_batch b, GemmKind kind) {
   return o.str();
 }
 
-// Picks (timing every feasible tile when tuning is on) the tile of one product
-// for the whole batch and uploads its work list.  The job table of `kind`
-// must already be on the device.
+// Launches one product of the batch: the work lists of its one or two tiles.
+hipError_t launch_batch_gemm(qmk_batch b, GemmKind kind, const BatchTiles& tiles, size_t n_first, size_t n_items,
+                             hipStream_t s) {
+  const int k = static_cast<int>(kind);
+  for (int q = 0; q < 2; ++q) {
+    const size_t n = q == 0 ? n_first : n_items - n_first;
+    if (n == 0) continue;
+    const int cfg = tiles.t[q];
+    const int grid =
+        persist_grid(b, gemm_persist_blocks_per_cu(kind, b->prec, cfg, b->tile_w32, b->tile_o32), n);
+    const hipError_t e = launch_gemm_persist(
+        kind, b->prec, cfg, b->d_g_jobs[k].as<GemmArgs>(), b->d_g_items[k].as<WorkItem>() + (q == 0 ? 0 : n_first),
+        static_cast<int>(n), grid, b->tile_w32, b->tile_o32, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// The work lists of a choice of tiles, on the device.
+qmk_status set_batch_items(qmk_batch b, GemmKind kind, const BatchTiles& tiles, hipStream_t s) {
+  const int k = static_cast<int>(kind);
+  if (tiles.t[1] < 0) {
+    b->g_items[k] = gemm_items(b, kind, tiles.t[0]);
+    b->g_first[k] = b->g_items[k].size();
+  } else {
+    b->g_items[k] = gemm_items(b, kind, tiles.t[0], &tiles);
+    b->g_first[k] = b->g_items[k].size();
+    const std::vector<WorkItem> rest = gemm_items(b, kind, tiles.t[1], &tiles);
+    b->g_items[k].insert(b->g_items[k].end(), rest.begin(), rest.end());
+  }
+  QMK_BHIP(b, upload(b->d_g_items[k], b->g_items[k], s), "upload work list");
+  return QMK_OK;
+}
+
+// Picks the tiles of one product for the whole batch and uploads its work
+// lists.  The job table of `kind` must already be on the device.  With tuning
+// on every feasible tile is timed on all molecules; the times per padded work
+// then say what each molecule would cost with each tile, and the four best
+// pairs by that estimate are timed too, every molecule with its better tile.
+// One tile pads the rows and columns of molecules of all sizes to half as much
+// again (24 molecules of 75 to 560 AOs: 1.45 to 1.5 of the outputs with the
+// wide tiles).  With pairs that batch takes 11.08 ms in FP64, 11.36 with one
+// tile; 48 molecules in BF16x3 5.97 and 6.18 ms.
 qmk_status choose_batch_tile(qmk_batch b, GemmKind kind, hipStream_t s) {
   const int k = static_cast<int>(kind);
-  if (b->tile[k] >= 0) return QMK_OK;
+  if (b->tile[k].t[0] >= 0) return QMK_OK;
   const std::string key = batch_key(b, kind);
   // the pre-split kernel addresses its tiles by 32-bit offsets: every job's
   // strides must fit the tile
+  const int n_tiles = gemm_num_tiles(b->prec);
   auto usable = [&](int cfg) {
-    if (!tile_feasible(b->prec, cfg)) return false;
+    if (cfg < 0 || cfg >= n_tiles || !tile_feasible(b->prec, cfg)) return false;
     if (b->prec != Prec::kBF16P) return true;
     for (const GemmArgs& g : b->g_jobs[k])
       if (!gemm_bf16p_args_ok(cfg, g)) return false;
     return true;
   };
-  int best = tune_cache_get(key);
-  if (best < 0 || best >= gemm_num_tiles(b->prec) || !usable(best)) {
-    best = -1;
+  BatchTiles best = BatchTiles::of(tune_cache_get(key));
+  if (!usable(best.t[0]) || (best.t[1] >= 0 && (!usable(best.t[1]) || best.ratio < 1))) {
+    best = BatchTiles();
     float best_ms = -1.0f;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     QMK_BHIP(b, hipEventCreate(&e0), "event");
     QMK_BHIP(b, hipEventCreate(&e1), "event");
-    for (int cfg = 0; cfg < gemm_num_tiles(b->prec); ++cfg) {
-      if (!usable(cfg)) continue;
-      if (best < 0) best = cfg;
-      if (!tuning_on()) break;
-      std::vector<WorkItem> items = gemm_items(b, kind, cfg);
-      QMK_BHIP(b, upload(b->d_g_items[k], items, s), "upload work list");
-      const int grid = persist_grid(
-          b, gemm_persist_blocks_per_cu(kind, b->prec, cfg, b->tile_w32, b->tile_o32), items.size());
-      auto run = [&]() {
-        return launch_gemm_persist(kind, b->prec, cfg, b->d_g_jobs[k].as<GemmArgs>(),
-                                   b->d_g_items[k].as<WorkItem>(), static_cast<int>(items.size()),
-                                   grid, b->tile_w32, b->tile_o32, s);
-      };
+    auto trial = [&](const BatchTiles& tiles, float* ms) -> qmk_status {
+      const qmk_status st = set_batch_items(b, kind, tiles, s);
+      if (st != QMK_OK) return st;
+      auto run = [&]() { return launch_batch_gemm(b, kind, tiles, b->g_first[k], b->g_items[k].size(), s); };
       QMK_BHIP(b, run(), "tile trial");
       QMK_BHIP(b, hipEventRecord(e0, s), "event");
       QMK_BHIP(b, run(), "tile trial");
       QMK_BHIP(b, hipEventRecord(e1, s), "event");
       QMK_BHIP(b, hipEventSynchronize(e1), "tile trial");
-      float ms = 0.0f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      if (best_ms < 0.0f || ms < best_ms) {
-        best_ms = ms;
-        best = cfg;
+      (void)hipEventElapsedTime(ms, e0, e1);
+      if (best_ms < 0.0f || *ms < best_ms) {
+        best_ms = *ms;
+        best = tiles;
       }
+      return QMK_OK;
+    };
+    std::vector<int> timed;
+    std::vector<double> rate(n_tiles, 0.0);  // time per padded work
+    qmk_status st = QMK_OK;
+    for (int cfg = 0; st == QMK_OK && cfg < n_tiles; ++cfg) {
+      if (!usable(cfg)) continue;
+      BatchTiles one;
+      one.t[0] = cfg;
+      if (best.t[0] < 0) best = one;
+      if (!tuning_on()) break;
+      float ms = 0.0f;
+      st = trial(one, &ms);
+      double work = 0.0;
+      for (const MolPlan& mp : b->plan) work += tile_work(b, kind, mp, cfg);
+      rate[cfg] = ms / std::max(work, 1.0);
+      if (ms > 0.0f) timed.push_back(cfg);
+    }
+    std::vector<std::pair<double, BatchTiles>> pairs;
+    for (size_t i = 0; i < timed.size(); ++i)
+      for (size_t j = i + 1; j < timed.size(); ++j) {
+        BatchTiles two;
+        two.t[0] = timed[i];
+        two.t[1] = timed[j];
+        two.ratio = static_cast<int>(std::clamp(64.0 * rate[timed[j]] / rate[timed[i]] + 0.5, 1.0, 2047.0));
+        double est = 0.0;
+        for (const MolPlan& mp : b->plan) {
+          const int t = tile_of(b, kind, mp, two);
+          est += rate[t] * tile_work(b, kind, mp, t);
+        }
+        if (est < best_ms) pairs.push_back({est, two});
+      }
+    std::stable_sort(pairs.begin(), pairs.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
+    for (size_t i = 0; st == QMK_OK && i < std::min<size_t>(pairs.size(), 4); ++i) {
+      float ms = 0.0f;
+      st = trial(pairs[i].second, &ms);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (best < 0) return bfail(b, QMK_UNSUPPORTED, "no tile fits in LDS and the operands' strides");
-    tune_cache_put(key, best);
+    if (st != QMK_OK) return st;
+    if (best.t[0] < 0) return bfail(b, QMK_UNSUPPORTED, "no tile fits in LDS and the operands' strides");
+    tune_cache_put(key, best.code());
   }
   b->tile[k] = best;
-  b->g_items[k] = gemm_items(b, kind, best);
-  QMK_BHIP(b, upload(b->d_g_items[k], b->g_items[k], s), "upload work list");
-  return QMK_OK;
+  return set_batch_items(b, kind, best, s);
 }
 
 // Enqueues the whole batch (forward, and the adjoint when with_adj).
@@ -463,13 +569,7 @@ qmk_status enqueue_all(qmk_batch b, bool with_adj, hipStream_t s) {
            "batch AO stage");
   auto gemm = [&](GemmKind kind) -> hipError_t {
     const int k = static_cast<int>(kind);
-    const int cfg = b->tile[k];
-    const int grid = persist_grid(
-        b, gemm_persist_blocks_per_cu(kind, b->prec, cfg, b->tile_w32, b->tile_o32), b->g_items[k].size());
-    return launch_gemm_persist(kind, b->prec, cfg, b->d_g_jobs[k].as<GemmArgs>(),
-                               b->d_g_items[k].as<WorkItem>(),
-                               static_cast<int>(b->g_items[k].size()), grid, b->tile_w32,
-                               b->tile_o32, s);
+    return launch_batch_gemm(b, kind, b->tile[k], b->g_first[k], b->g_items[k].size(), s);
   };
   QMK_BHIP(b, gemm(GemmKind::kForward), "batch contraction");
   if (!with_adj) return QMK_OK;
@@ -591,7 +691,7 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
   const int o32 = dtype == QMK_F32;
   const int w32 = o32;  // weights have the output's element type
   if (b->tile_o32 != o32 || b->tile_w32 != w32) {
-    b->tile[0] = b->tile[1] = b->tile[2] = -1;
+    for (BatchTiles& t : b->tile) t = BatchTiles();
     b->tile_o32 = o32;
     b->tile_w32 = w32;
     drop_graph(b);
