@@ -220,9 +220,40 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
       act_was = out.act_prev[blk * out.act_words + lane];
     }
   }
+  // SCR = 2: bit s of want says that shell s of the group has a chunk active now
+  // or before (its 10 AOs at most lie in two chunks), found by 64 lanes at
+  // once; few have, and one scalar test passes over each of the others (7500 AOs,
+  // 63,000 points: store pass 296 us with a test of its own for every shell, 199
+  // so; up to 128 shells in a group and 64 of a nucleus).
+  uint64_t want[2] = {0, 0};
+  const bool listed = SCR == 2 && out.act_words <= 64 && ns <= 128;
+  if constexpr (SCR == 2) {
+    if (listed) {
+      const uint32_t either = act_now | act_was;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int q = 64 * h + (threadIdx.x & 63);
+        const ShellDev sh = s_shell[q < ns ? q : 0];
+        const int c0 = sh.ao_off / kSparseChunk;
+        const int c1 = (sh.ao_off + (sh.l + 1) * (sh.l + 2) / 2 - 1) / kSparseChunk;
+        const uint32_t on = (static_cast<uint32_t>(__shfl(static_cast<int>(either), c0 >> 5, 64)) >> (c0 & 31)) |
+                            (static_cast<uint32_t>(__shfl(static_cast<int>(either), c1 >> 5, 64)) >> (c1 & 31));
+        want[h] = __ballot(q < ns && (on & 1u));
+      }
+    }
+  }
 
   for (int a = 0; a < nn; ++a) {
     const NucDev nu = s_nuc[a];
+    uint64_t todo = ~uint64_t(0);  // SCR = 2: want of the nucleus' shells (up to 64 of them)
+    if constexpr (SCR == 2) {
+      const int b0 = __builtin_amdgcn_readfirstlane(nu.sh_begin), n = __builtin_amdgcn_readfirstlane(nu.sh_end) - b0;
+      if (listed && n <= 64) {
+        todo = b0 >= 64 ? want[1] >> (b0 - 64) : (b0 == 0 ? want[0] : (want[0] >> b0) | (want[1] << (64 - b0)));
+        if (n < 64) todo &= (uint64_t(1) << n) - 1;
+        if (todo == 0) continue;
+      }
+    }
     const double dx = rx - nu.x, dy = ry - nu.y, dz = rz - nu.z;
     const double u = dist2(dx, dy, dz);
     const bool near = valid && (nu.gmin * u < T);
@@ -249,6 +280,10 @@ __device__ __forceinline__ void ao_vgl_body(const AoTables& t, const PointArgs& 
       continue;
     }
     for (int s = nu.sh_begin + z; s < nu.sh_end; s += nz) {
+      if constexpr (SCR == 2) {
+        const int q = __builtin_amdgcn_readfirstlane(s - nu.sh_begin);
+        if (q < 64 && !((todo >> q) & 1)) continue;
+      }
       const ShellDev sh = s_shell[s];
       if constexpr (SCR == 2) {
         // the wave's block: chunks of this shell active now, or before

@@ -123,3 +123,29 @@ def test_device_parameters_and_batch(swap):
         for k in ("d_coef", "d_elec", "d_nucl"):
             assert grad_err(g[k].cpu().numpy().reshape(ref[k].shape), ref[k], ref[k + "_abs"]) <= 1e-11, k
     b.close()
+
+
+@pytest.mark.parametrize("shells", [63, 64, 65, 128, 129, 200])
+def test_screened_store_with_many_shells_on_a_nucleus(shells):
+    """The screened AO store finds a group's shells to store 64 at a time, up to
+    128 in a group: the screened result equals the dense one, also when the
+    points move away and back (chunks become zero and non-zero again)."""
+    import paper_2512_16677_amd as q
+    s = synth.water_like(walkers=2)
+    rng = np.random.default_rng(shells)
+    nuc = np.sort(np.r_[np.zeros(shells, int), rng.integers(1, 3, 40)])
+    n = len(nuc)
+    s.nucl_coord = np.array([[0.0, 0.0, 0.0], [9.0, 0.0, 0.0], [0.0, 14.0, 0.0]])
+    s.shell_nucleus, s.shell_ang_mom = nuc, rng.integers(0, 2, n)
+    s.shell_prim_offset = np.arange(n + 1)
+    s.exponent, s.coefficient = 10.0 ** rng.uniform(-1.0, 2.5, n), np.ones(n)
+    s.mo_coef = rng.normal(0.0, 0.1, size=(11, s.ao_num))
+    ctx = q.Context.from_system(s, bits=24)
+    for step in (0.0, 30.0, 3.0, 0.0):
+        pts = (s.nucl_coord[rng.integers(0, 3, 200)] + rng.normal(size=(200, 3)) + step).reshape(1, 200, 3)
+        ctx.set_point(pts)
+        ctx.set_screening(False)
+        dense = ctx.get_mo_vgl()
+        ctx.set_screening(True)
+        assert bool((ctx.get_mo_vgl() == dense).all())
+    ctx.close()
