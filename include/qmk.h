@@ -25,6 +25,11 @@
  *     managed memory, or pinned host memory mapped for the device.  Other
  *     pointers (pageable host memory) are rejected with
  *     QMK_INVALID_ARG_BASE + k before any work is enqueued.
+ *   - Calls that are enqueued keep the inputs that they were made with: a
+ *     set_* call, on return, has either left the copies that they read alone
+ *     or waited for them.  The context's intermediates (AO arrays, workspaces)
+ *     are shared by its calls, so a caller that uses several streams with one
+ *     context orders its calls on them.
  *   - A context is not thread-safe: use one context per host thread, as in
  *     the paper's parallelisation model (Section 2.4).  Contexts are
  *     independent of each other (Section 2.2).

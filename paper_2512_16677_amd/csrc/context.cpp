@@ -90,6 +90,28 @@ qmk_status check_dev_arg(qmk_ctx ctx, int k, const void* p) {
   return QMK_OK;
 }
 
+void use_stream(qmk_ctx ctx, hipStream_t s) {
+  if (ctx->stream_used && ctx->stream != s) ctx->other_streams = true;
+  ctx->stream = s;
+  ctx->stream_used = true;
+}
+
+qmk_status wait_other_streams(qmk_ctx ctx) {
+  if (!ctx->other_streams) return QMK_OK;
+  QMK_HIP(ctx, hipDeviceSynchronize(), "wait for the context's streams");
+  ctx->other_streams = false;
+  return QMK_OK;
+}
+
+qmk_status wait_own_work(qmk_ctx ctx) {
+  if (!ctx->stream_used) return QMK_OK;
+  if (ctx->other_streams) return wait_other_streams(ctx);
+  if (hipStreamSynchronize(ctx->stream) == hipSuccess) return QMK_OK;
+  (void)hipGetLastError();  // the caller has destroyed the stream of an earlier call
+  QMK_HIP(ctx, hipDeviceSynchronize(), "wait for the context's work");
+  return QMK_OK;
+}
+
 hipEvent_t take_event(qmk_ctx ctx) {
   if (!ctx->event_pool.empty()) {
     hipEvent_t e = ctx->event_pool.back();
@@ -277,7 +299,7 @@ std::vector<int64_t> order_rows(qmk_ctx ctx, const std::vector<double>& nucl) {
 }
 
 // Builds the device nucleus / shell / primitive tables and nucleus groups.
-qmk_status build_tables(qmk_ctx ctx, hipStream_t stream, bool* relay) {
+qmk_status build_tables(qmk_ctx ctx, bool* relay) {
   const int64_t S = ctx->shell_num;
   std::vector<std::vector<int64_t>> shells_of(ctx->nucl_num);
   for (int64_t s = 0; s < S; ++s) shells_of[ctx->sh_nuc[s]].push_back(s);
@@ -356,6 +378,9 @@ qmk_status build_tables(qmk_ctx ctx, hipStream_t stream, bool* relay) {
   close_group();
   if (group.empty()) return fail(ctx, QMK_NOT_SET, "basis has no shells");
 
+  // earlier calls may still be reading the tables
+  const qmk_status ws = wait_own_work(ctx);
+  if (ws != QMK_OK) return ws;
   auto up = [&](DevBuf& b, const void* src, size_t n) -> hipError_t {
     hipError_t e = b.ensure(n);
     if (e != hipSuccess) return e;
@@ -375,12 +400,10 @@ qmk_status build_tables(qmk_ctx ctx, hipStream_t stream, bool* relay) {
         ao_of[row[s] + i] = static_cast<int32_t>(ao_off[s] + i);
         af[row[s] + i] = ctx->af[ao_off[s] + i];
       }
-  // copies of C in another order of rows are laid out again; earlier work of
-  // the stream may still read them and the tables
+  // copies of C in another order of rows are laid out again
   const bool reorder = row_of != ctx->row_of;
   *relay = reorder && !ctx->coef_dirty;
   if (reorder) {
-    QMK_HIP(ctx, hipStreamSynchronize(stream), "new AO rows");
     ctx->coef_dirty = true;
     ctx->occ_coef_version = -1;
     ctx->row_of = row_of;
@@ -423,6 +446,8 @@ qmk_status build_tables(qmk_ctx ctx, hipStream_t stream, bool* relay) {
 // FP64 coefficients on the device.  Waits for them, so that every stream
 // may read them afterwards (as after the upload).
 qmk_status make_coef_copies(qmk_ctx ctx, const double* src, hipStream_t s) {
+  const qmk_status ws = wait_other_streams(ctx);  // earlier calls may still be reading the copies
+  if (ws != QMK_OK) return ws;
   const int want = ctx->mode == QMK_FP64 ? 0 : (ctx->mode == QMK_MIXED_F32 ? 1 : 2);
   const int64_t K = ctx->ao_num, N = ctx->mo_num;
   ctx->Kp = round_up(K, kAoPad);
@@ -443,9 +468,10 @@ qmk_status make_coef_copies(qmk_ctx ctx, const double* src, hipStream_t s) {
 }
 
 qmk_status ensure_tables(qmk_ctx ctx, hipStream_t s) {
+  use_stream(ctx, s);
   if (ctx->tables_dirty) {
     bool relay = false;
-    qmk_status st = build_tables(ctx, s, &relay);
+    qmk_status st = build_tables(ctx, &relay);
     if (st == QMK_OK && relay && ctx->craw_valid) st = make_coef_copies(ctx, ctx->d_Craw.as<double>(), s);
     if (st != QMK_OK) return st;
   }
@@ -547,6 +573,7 @@ qmk_status provide_ao_sorted(qmk_ctx ctx, hipStream_t s, bool force = false) {
                 "the screened evaluation sorts points by nearest nucleus for at most " +
                     std::to_string(kSortMaxNuclei) + " nuclei");
   if (ctx->nuc_curve_version != ctx->geom_version) {
+    if ((st = wait_own_work(ctx)) != QMK_OK) return st;
     const std::vector<size_t> order = curve_order(ctx->nucl);
     std::vector<double> xyz(static_cast<size_t>(3 * nn));
     for (int64_t k = 0; k < nn; ++k)
@@ -676,7 +703,7 @@ qmk_status ensure_cusp(qmk_ctx ctx, hipStream_t s) {
   const int64_t key[4] = {ctx->geom_version, ctx->coef_version, ctx->cusp_version, ctx->mode};
   if (std::equal(key, key + 4, ctx->cusp_key)) return QMK_OK;
   qmk_status st = ensure_tables(ctx, s);
-  if (st != QMK_OK || (st = host_coef(ctx)) != QMK_OK) return st;
+  if (st != QMK_OK || (st = host_coef(ctx)) != QMK_OK || (st = wait_own_work(ctx)) != QMK_OK) return st;
   const int64_t nn = ctx->nucl_num, K = ctx->ao_num, N = ctx->mo_num;
   const double* R = ctx->nucl.data();
   for (int64_t a = 0; a < nn; ++a)
@@ -1161,6 +1188,8 @@ qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* co
   qmk_status st;
   if ((st = check_dev_arg(ctx, 3, coord)) != QMK_OK || (st = check_dev_arg(ctx, 6, coef)) != QMK_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  use_stream(ctx, s);
+  if ((st = wait_other_streams(ctx)) != QMK_OK) return st;  // nuclei and copies of C are written in place
   const int64_t n = mo_num * ao_num, n3 = 3 * nucl_num;
   const size_t pin_need = 16 + static_cast<size_t>(n3) * 8;
   if (ctx->pin_bytes < pin_need) {
@@ -1300,7 +1329,9 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
   const int kmax = static_cast<int>(nord - 2), mh = static_cast<int>(nord / 2), deg = static_cast<int>(nord);
   const size_t nq = static_cast<size_t>((kmax + 1) * mh * nn * kJasCoef);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  use_stream(ctx, s);
   if (ctx->nuc_xyz_version != ctx->geom_version) {
+    if ((st = wait_own_work(ctx)) != QMK_OK) return st;
     QMK_HIP(ctx, ctx->d_nuc_xyz.ensure(static_cast<size_t>(3 * nn) * 8), "alloc nuclei");
     QMK_HIP(ctx, hipMemcpy(ctx->d_nuc_xyz.p, ctx->nucl.data(), static_cast<size_t>(3 * nn) * 8,
                            hipMemcpyHostToDevice), "upload nuclei");
@@ -1333,8 +1364,8 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
           q[((static_cast<int64_t>(k) * mh + (m - 1)) * nn + a) * kJasCoef + e] = c[t * nn + a];
       }
     }
-    // the previous call's kernels on this stream may still read the tables
-    QMK_HIP(ctx, hipStreamSynchronize(s), "wait for the previous Jastrow call");
+    // the previous call's kernels may still read the tables
+    if ((st = wait_own_work(ctx)) != QMK_OK) return st;
     QMK_HIP(ctx, ctx->een_q.ensure((q.size() + q0.size()) * 8), "alloc weight polynomials");
     QMK_HIP(ctx, hipMemcpy(ctx->een_q.p, q.data(), q.size() * 8, hipMemcpyHostToDevice), "upload weight polynomials");
     QMK_HIP(ctx, hipMemcpy(ctx->een_q.as<double>() + q.size(), q0.data(), q0.size() * 8, hipMemcpyHostToDevice),
@@ -1445,6 +1476,8 @@ qmk_status qmk_set_point(qmk_ctx ctx, char transp, int64_t walk_num, int64_t ele
     for (int64_t i = 0; i < n; ++i)
       if (!std::isfinite(coord[i])) return fail(ctx, QMK_NONFINITE, "non-finite coordinate");
     DeviceGuard g(ctx->device);
+    const qmk_status st = wait_own_work(ctx);  // earlier calls may still be reading the points
+    if (st != QMK_OK) return st;
     QMK_HIP(ctx, ctx->own_pts.ensure(static_cast<size_t>(n) * sizeof(double)), "alloc points");
     QMK_HIP(ctx, hipMemcpy(ctx->own_pts.p, coord, n * sizeof(double), hipMemcpyHostToDevice),
             "upload points");
@@ -1714,6 +1747,7 @@ qmk_status qmk_get_density(qmk_ctx ctx, const double* occ, int64_t occ_num, doub
       }
     }
     const size_t cb = static_cast<size_t>(Kp * Nop) * (f32 ? 4 : 8);
+    if ((st = wait_own_work(ctx)) != QMK_OK) return st;  // an earlier density may still be reading them
     QMK_HIP(ctx, ctx->d_Cocc_t.ensure(cb), "alloc occupied coefficients");
     QMK_HIP(ctx, hipMemcpy(ctx->d_Cocc_t.p, f32 ? static_cast<const void*>(ct32.data())
                                                  : static_cast<const void*>(ct64.data()),

@@ -171,6 +171,11 @@ struct qmk_ctx_s {
   int64_t gbar_Pp = 0, gbar_Kp = 0;
   int gbar_f32 = -1;
 
+  // stream of the last call, and whether earlier ones used others since the
+  // context last waited for all of them (wait_own_work)
+  hipStream_t stream = nullptr;
+  bool stream_used = false, other_streams = false;
+
   int64_t launches = 0;
   int forced_tile[5] = {-1, -1, -1, -1, -1};  // per GemmKind; -1 = autotuned
 
@@ -219,6 +224,15 @@ qmk_status bad_arg(qmk_ctx ctx, int k, const std::string& msg);
 qmk_status check_dev_arg(qmk_ctx ctx, int k, const void* p);
 qmk_status hip_fail(qmk_ctx ctx, hipError_t e, const char* what);
 bool valid_ctx(qmk_ctx ctx);
+// Every call that enqueues work of a context names its stream first (use_stream).
+// Device copies that calls share (tables, coefficients, points) are rewritten
+// by blocking copies on the null stream, which do not wait for non-blocking
+// streams (torch's side streams), or by kernels on the new call's stream:
+// before the former the context waits for all of its work (wait_own_work), before
+// the latter for its work on other streams (wait_other_streams).
+void use_stream(qmk_ctx ctx, hipStream_t s);
+qmk_status wait_own_work(qmk_ctx ctx);
+qmk_status wait_other_streams(qmk_ctx ctx);
 qmk_status ensure_tables(qmk_ctx ctx, hipStream_t s);
 // s: the stream that the copies are made on (complete on return).
 qmk_status ensure_coef(qmk_ctx ctx, hipStream_t s);
