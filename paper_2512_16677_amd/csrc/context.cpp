@@ -1206,31 +1206,45 @@ qmk_status qmk_set_params_device(qmk_ctx ctx, int64_t nucl_num, const double* co
   // the tables keep their shape when the nuclei move: their centres are
   // written in place, unless the tables are to be built anyway
   const bool move = !ctx->tables_dirty, ordered = ctx->ao_num >= kOrderRowsAo;
+  const bool had_copies = ctx->has_coef && !ctx->coef_dirty;
   ctx->tables_dirty = true;  // until the new centres are accepted
   QMK_HIP(ctx, launch_take_params(coef, ctx->d_Craw_new.as<double>(), n, coord, nucl_num, host_xyz,
                                   move ? ctx->d_nuc.as<NucDev>() : nullptr, move ? ctx->nucl_dev : 0, flag, s),
           "take parameters");
   // the products' copies of C are made before they are known to be finite, so
-  // that there is one wait; refused ones are laid out again from the kept C
+  // that there is one wait; after refused values the tables and the copies
+  // that the call replaced are made again from the kept ones.  Copies that
+  // outgrow their buffers are left to the next call, so that refused values
+  // never move them (captured work may hold their addresses); those of
+  // ordered rows too, because the order follows the nuclei.
+  const size_t n_pad = static_cast<size_t>(round_up(mo_num, kMoPad) * round_up(ao_num, kAoPad));
+  bool now = !ordered;
+  for (const DevBuf* b : {&ctx->d_Ct, &ctx->d_C}) now = now && (!b->p || b->bytes >= n_pad * (ctx->mode ? 4 : 8));
+  for (const DevBuf* b : {&ctx->d_Cb_hi, &ctx->d_Cb_lo, &ctx->d_Ctb_hi, &ctx->d_Ctb_lo})
+    now = now && (!b->p || b->bytes >= n_pad * 2);
   const int64_t mo_before = ctx->mo_num;
   ctx->mo_num = mo_num;
   ctx->coef_dirty = true;
-  if (!ordered) {
+  if (now) {
     st = make_coef_copies(ctx, ctx->d_Craw_new.as<double>(), s);
     if (st != QMK_OK) {
       ctx->mo_num = mo_before;
       ctx->coef_dirty = true;
       return st;
     }
-  } else {  // their rows' order follows the nuclei
+  } else {
     QMK_HIP(ctx, hipStreamSynchronize(s), "take parameters");
   }
   for (int64_t i = 0; st == QMK_OK && i < n3; ++i)
     if (!std::isfinite(host_xyz[i])) st = fail(ctx, QMK_NONFINITE, "non-finite nuclear coordinate");
   if (st == QMK_OK && *flag) st = fail(ctx, QMK_NONFINITE, "non-finite MO coefficient");
   if (st != QMK_OK) {
+    const std::string why = ctx->err;
     ctx->mo_num = mo_before;
-    ctx->coef_dirty = true;
+    bool relay = false;
+    const bool back = !move || build_tables(ctx, &relay) == QMK_OK;
+    if (back && had_copies) (void)make_coef_copies(ctx, ctx->d_Craw.as<double>(), s);
+    ctx->err = why;
     return st;
   }
   ctx->nucl.assign(host_xyz, host_xyz + n3);
