@@ -1146,6 +1146,9 @@ qmk_status qmk_set_basis(qmk_ctx ctx, int64_t shell_num, int64_t prim_num,
         }
     }
   }
+  // the products read whole steps of 32 rows: rows that held AOs of another
+  // basis are cleared again (0 times an infinite one is not 0)
+  if (ao_num != ctx->ao_num) ctx->ao_Pp = ctx->aov_Pp = ctx->aos_Pp = 0;
   ctx->shell_num = shell_num;
   ctx->prim_num = prim_num;
   ctx->ao_num = ao_num;
