@@ -148,7 +148,8 @@ __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restri
                                                           CoefCopies o) {
   typedef typename std::conditional<MODE == 0, double, float>::type T;
   __shared__ double tile[32][33];
-  const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 32, n0 = static_cast<int64_t>(blockIdx.y) * 32;
+  const uint32_t kb = static_cast<uint32_t>(Kp / 32), nb = blockIdx.x / kb;
+  const int64_t k0 = static_cast<int64_t>(blockIdx.x - nb * kb) * 32, n0 = static_cast<int64_t>(nb) * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   auto put = [](const CoefCopies& c, bool transposed, int64_t at, int64_t slab_at, double v) {
     static_cast<T*>(transposed ? c.ct : c.c)[at] = static_cast<T>(v);
@@ -209,8 +210,9 @@ __global__ __launch_bounds__(256) void take_params_kernel(const double* __restri
 hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
                               const int32_t* ao_of, const CoefCopies& o, hipStream_t s) {
   if (N <= 0 || K <= 0) return hipSuccess;
-  if (Np % 32 != 0 || Kp % 32 != 0 || Np < N || Kp < K || Np / 32 > 65535) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(Kp / 32), static_cast<unsigned>(Np / 32));
+  if (Np % 32 != 0 || Kp % 32 != 0 || Np < N || Kp < K || (Np / 32) * (Kp / 32) > 0x7fffffff)
+    return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>((Np / 32) * (Kp / 32)));
   if (mode == 0)
     hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
   else if (mode == 1)
