@@ -132,7 +132,8 @@ __global__ __launch_bounds__(256) void split_w_batch_kernel(const SplitJob* __re
 // The products' copies of C [N][K] (FP64): C [Np][Kp] and C^T [Kp][Np] in FP64
 // (MODE 0) or FP32 (1, 2), and in MODE 2 both split into bf16 hi / lo planes
 // (hi = bf16(c), lo = bf16(c - hi), the residual in FP64); zeros beyond N
-// and K; row k of the copies is the caller's AO ao_of[k].  Np and Kp are
+// and K; row k of the copies is the caller's AO ao_of[k], column n the caller's
+// MO mo_of[n] (the density's occupied ones, which need C^T only).  Np and Kp are
 // multiples of 32.  The planes are in slabs of 32 reduction indices, [Kp / 32]
 // [Np][32] of C and [Np / 32][Kp][32] of C^T: a K step of a product's tile is
 // one run of memory (with rows of Kp or Np, 64 bytes of every row: 7500-AO
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(256) void split_w_batch_kernel(const SplitJob* __re
 template <int MODE>
 __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restrict__ src, int64_t N, int64_t K,
                                                           int64_t Np, int64_t Kp, const int32_t* __restrict__ ao_of,
-                                                          CoefCopies o) {
+                                                          const int32_t* __restrict__ mo_of, CoefCopies o) {
   typedef typename std::conditional<MODE == 0, double, float>::type T;
   __shared__ double tile[32][33];
   const uint32_t kb = static_cast<uint32_t>(Kp / 32), nb = blockIdx.x / kb;
@@ -167,8 +168,8 @@ __global__ __launch_bounds__(256) void coef_layout_kernel(const double* __restri
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int64_t n = n0 + ty + 8 * q, k = k0 + tx;
-    const double v = n < N && k < K ? src[n * K + (ao_of ? ao_of[k] : k)] : 0.0;
-    put(o, false, n * Kp + k, k0 * Np + n * 32 + tx, v);
+    const double v = n < N && k < K ? src[(mo_of ? mo_of[n] : n) * K + (ao_of ? ao_of[k] : k)] : 0.0;
+    if (o.c) put(o, false, n * Kp + k, k0 * Np + n * 32 + tx, v);
     tile[ty + 8 * q][tx] = v;
   }
   __syncthreads();
@@ -208,17 +209,17 @@ __global__ __launch_bounds__(256) void take_params_kernel(const double* __restri
 }  // namespace
 
 hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
-                              const int32_t* ao_of, const CoefCopies& o, hipStream_t s) {
+                              const int32_t* ao_of, const int32_t* mo_of, const CoefCopies& o, hipStream_t s) {
   if (N <= 0 || K <= 0) return hipSuccess;
   if (Np % 32 != 0 || Kp % 32 != 0 || Np < N || Kp < K || (Np / 32) * (Kp / 32) > 0x7fffffff)
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>((Np / 32) * (Kp / 32)));
   if (mode == 0)
-    hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
+    hipLaunchKernelGGL(coef_layout_kernel<0>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, mo_of, o);
   else if (mode == 1)
-    hipLaunchKernelGGL(coef_layout_kernel<1>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
+    hipLaunchKernelGGL(coef_layout_kernel<1>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, mo_of, o);
   else
-    hipLaunchKernelGGL(coef_layout_kernel<2>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, o);
+    hipLaunchKernelGGL(coef_layout_kernel<2>, grid, dim3(256), 0, s, src, N, K, Np, Kp, ao_of, mo_of, o);
   return hipGetLastError();
 }
 

@@ -131,8 +131,10 @@ struct qmk_ctx_s {
   int64_t aov_Pp = 0, aov_Kp = 0, aov_date = -1;
   int aov_f32 = -1;
 
-  // density: occupied MOs compacted into Cocc^T [Kp][No_p] and occ [No_p]
-  DevBuf d_Cocc_t, d_occ, ws_den;
+  // density: occupied MOs (d_occ_mo) compacted into Cocc^T [Kp][No_p], laid out
+  // for the current AO rows where occ_laid, and occ [No_p]
+  DevBuf d_Cocc_t, d_occ, d_occ_mo, ws_den;
+  bool occ_laid = false;
   std::vector<double> occ_key;
   int64_t occ_coef_version = -1, n_occ = 0, Nop = 0;
   int occ_f32 = -1;

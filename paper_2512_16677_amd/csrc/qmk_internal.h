@@ -371,9 +371,10 @@ struct CoefCopies {
   void *c_hi, *c_lo, *ct_hi, *ct_lo;
 };
 // mode: 0 FP64, 1 FP32, 2 FP32 and bf16 planes.  ao_of: the caller's AO of every
-// row k of the copies (NULL: k).
+// row k of the copies (NULL: k); mo_of: the caller's MO of each of the N columns
+// (NULL: n).  Modes 0 and 1 leave c out where it is NULL.
 hipError_t launch_coef_layout(const double* src, int64_t N, int64_t K, int64_t Np, int64_t Kp, int mode,
-                              const int32_t* ao_of, const CoefCopies& o, hipStream_t s);
+                              const int32_t* ao_of, const int32_t* mo_of, const CoefCopies& o, hipStream_t s);
 // n coefficients to coef_out, with *flag = 1 (device-visible, cleared by the
 // caller) if one is not finite; n_nucl nuclei to nucl_out and, unless nuc is
 // NULL, into the n_nuc entries of the nucleus table.
