@@ -62,33 +62,6 @@ hipError_t upload(DevBuf& b, const std::vector<T>& v, hipStream_t s) {
   return hipMemcpyAsync(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
 }
 
-// A table inside the batch's one device buffer of job tables.
-struct TabPtr {
-  void* p = nullptr;
-  template <typename T>
-  T* as() const { return static_cast<T*>(p); }
-};
-
-// Collects the job tables of a run, so that one copy uploads them all (a copy
-// per table was a launch and a gap on the stream for each of thirteen).
-struct TableSet {
-  std::vector<unsigned char> bytes;
-  std::vector<std::pair<TabPtr*, size_t>> at;
-  template <typename T>
-  void add(TabPtr& t, const std::vector<T>& v) {
-    const size_t off = (bytes.size() + 255) / 256 * 256;
-    bytes.resize(off + std::max<size_t>(v.size() * sizeof(T), 16));
-    if (!v.empty()) std::memcpy(bytes.data() + off, v.data(), v.size() * sizeof(T));
-    at.push_back({&t, off});
-  }
-  hipError_t upload(DevBuf& b, hipStream_t s) {
-    const hipError_t e = b.ensure(bytes.size());
-    if (e != hipSuccess) return e;
-    for (auto& a : at) a.first->p = static_cast<unsigned char*>(b.p) + a.second;
-    return hipMemcpyAsync(b.p, bytes.data(), bytes.size(), hipMemcpyHostToDevice, s);
-  }
-};
-
 }  // namespace
 
 // The tiles of one batched product: t[0], and t[1] (-1: none) for the
@@ -792,7 +765,9 @@ qmk_status qmk_batch_run(qmk_batch b, void* const* outs, int32_t dtype, const vo
     b->n_nred = static_cast<int>(nred.size());
     b->nred_total = nred_prefix.back();
   }
-  QMK_BHIP(b, tables.upload(b->d_tables, s), "upload jobs");
+  QMK_BHIP(b, tables.place(b->d_tables), "alloc job tables");
+  QMK_BHIP(b, hipMemcpyAsync(b->d_tables.p, tables.bytes.data(), tables.bytes.size(), hipMemcpyHostToDevice, s),
+           "upload jobs");
 
   for (int k = 0; k < 3; ++k) b->g_jobs[k] = gj[k];
 

@@ -229,26 +229,48 @@ std::vector<size_t> curve_order(const std::vector<double>& nucl) {
 // classes, and a 256-point tile visits 0.12 of its K steps, 0.27 with the rows
 // in the caller's order, where nearly every step holds a diffuse shell;
 // BF16x3 forward pass 2.5 ms, 4.2 ms in the caller's order.
+// Only the places depend on the nuclei: what the basis decides is kept
+// (RowPlan), so that a new geometry sorts its nuclei and no shells.
+void make_row_plan(qmk_ctx ctx) {
+  // bins of the smallest exponent, a quarter octave wide, the widest shells first
+  constexpr int kBins = 256;
+  constexpr double kReachArg = 25.0;  // exponent argument at the reach
+  const int64_t S = ctx->shell_num;
+  auto& plan = ctx->row_plan;
+  plan = {};
+  plan.bin.resize(S);
+  std::vector<double> gmin(S, INFINITY), rows(kBins, 0.0), reach(kBins, 0.0);
+  for (int64_t s = 0; s < S; ++s) {
+    for (int64_t k = ctx->sh_off[s]; k < ctx->sh_off[s + 1]; ++k) gmin[s] = std::min(gmin[s], ctx->expo[k]);
+    const int b = static_cast<int>(std::clamp(4.0 * std::log2(gmin[s]) + kBins / 2, 0.0, kBins - 1.0));
+    plan.bin[s] = b;
+    rows[b] += n_cart(ctx->sh_l[s]);
+    reach[b] = std::max(reach[b], std::sqrt(kReachArg / gmin[s]));
+  }
+  for (int b = 0; b < kBins; ++b)
+    if (rows[b] > 0.0) {
+      plan.used.push_back(b);
+      plan.rows.push_back(rows[b]);
+      plan.reach.push_back(reach[b]);
+    }
+  plan.of_nucleus.resize(S);
+  std::iota(plan.of_nucleus.begin(), plan.of_nucleus.end(), int64_t(0));
+  std::stable_sort(plan.of_nucleus.begin(), plan.of_nucleus.end(), [&](int64_t a, int64_t b) {
+    return ctx->sh_nuc[a] != ctx->sh_nuc[b] ? ctx->sh_nuc[a] < ctx->sh_nuc[b] : gmin[a] < gmin[b];
+  });
+  plan.first.assign(ctx->nucl_num + 1, 0);
+  for (int64_t s = 0; s < S; ++s) ++plan.first[ctx->sh_nuc[s] + 1];
+  for (int64_t A = 0; A < ctx->nucl_num; ++A) plan.first[A + 1] += plan.first[A];
+  plan.ready = true;
+}
+
 std::vector<int64_t> order_rows(qmk_ctx ctx, const std::vector<double>& nucl) {
   const int64_t S = ctx->shell_num;
-  std::vector<int64_t> order(S), row(S + 1);
-  std::iota(order.begin(), order.end(), int64_t(0));
+  std::vector<int64_t> order, row(S + 1);
   if (ctx->ao_num >= kOrderRowsAo) {
-    const std::vector<size_t> curve = curve_order(nucl);
-    std::vector<int64_t> rank(curve.size());
-    for (size_t i = 0; i < curve.size(); ++i) rank[curve[i]] = static_cast<int64_t>(i);
-    // bins of the smallest exponent, a quarter octave wide, the widest shells first
-    constexpr int kBins = 256;
-    constexpr double kReachArg = 25.0, kTile = 2.0;  // exponent argument at the reach; a tile's extent (bohr)
-    std::vector<double> gmin(S, INFINITY);
-    std::vector<int> bin(S);
-    std::vector<double> rows(kBins, 0.0), reach(kBins, 0.0);
-    for (int64_t s = 0; s < S; ++s) {
-      for (int64_t k = ctx->sh_off[s]; k < ctx->sh_off[s + 1]; ++k) gmin[s] = std::min(gmin[s], ctx->expo[k]);
-      bin[s] = static_cast<int>(std::clamp(4.0 * std::log2(gmin[s]) + kBins / 2, 0.0, kBins - 1.0));
-      rows[bin[s]] += n_cart(ctx->sh_l[s]);
-      if (std::isfinite(gmin[s])) reach[bin[s]] = std::max(reach[bin[s]], std::sqrt(kReachArg / gmin[s]));
-    }
+    if (!ctx->row_plan.ready) make_row_plan(ctx);
+    const auto& plan = ctx->row_plan;
+    constexpr double kTile = 2.0;  // a tile's extent (bohr)
     double volume = 1.0;
     for (int x = 0; x < 3; ++x) {
       double lo = nucl[x], hi = nucl[x];
@@ -258,19 +280,16 @@ std::vector<int64_t> order_rows(qmk_ctx ctx, const std::vector<double>& nucl) {
       }
       volume *= hi - lo + kTile;
     }
-    std::vector<int> used;
-    for (int i = 0; i < kBins; ++i)
-      if (rows[i] > 0.0) used.push_back(i);
     // best[j]: expected steps of the first j used bins in their best classes, the last of them from bin from[j]
-    const int n_used = static_cast<int>(used.size());
+    const int n_used = static_cast<int>(plan.used.size());
     std::vector<double> best(n_used + 1, INFINITY);
-    std::vector<int> from(n_used + 1, 0), cls(kBins, 0);
+    std::vector<int> from(n_used + 1, 0), ends;
     best[0] = 0.0;
     for (int j = 1; j <= n_used; ++j) {
       double r = 0.0, n = 0.0;
       for (int i = j - 1; i >= 0; --i) {
-        r = std::max(r, reach[used[i]]);
-        n += rows[used[i]];
+        r = std::max(r, plan.reach[i]);
+        n += plan.rows[i];
         const double steps = n / 32.0, side = std::cbrt(volume / steps) + 2.0 * r + kTile;
         const double met = std::min(steps, steps / volume * side * side * side) + 0.5;  // half a step shared
         if (best[i] + met < best[j]) {
@@ -279,15 +298,20 @@ std::vector<int64_t> order_rows(qmk_ctx ctx, const std::vector<double>& nucl) {
         }
       }
     }
-    for (int j = n_used; j > 0; j = from[j])
-      for (int i = from[j]; i < j; ++i) cls[used[i]] = from[j];
-    std::sort(order.begin(), order.end(), [&](int64_t a, int64_t b) {
-      if (cls[bin[a]] != cls[bin[b]]) return cls[bin[a]] < cls[bin[b]];
-      const int64_t ra = rank[ctx->sh_nuc[a]], rb = rank[ctx->sh_nuc[b]];
-      if (ra != rb) return ra < rb;
-      if (gmin[a] != gmin[b]) return gmin[a] < gmin[b];
-      return a < b;
-    });
+    for (int j = n_used; j > 0; j = from[j]) ends.push_back(j);
+    const std::vector<size_t> curve = curve_order(nucl);
+    order.reserve(S);
+    for (size_t c = ends.size(); c-- > 0;) {
+      const int lo = plan.used[from[ends[c]]], hi = plan.used[ends[c] - 1];
+      for (size_t A : curve)
+        for (int64_t k = plan.first[A]; k < plan.first[A + 1]; ++k) {
+          const int64_t s = plan.of_nucleus[k];
+          if (plan.bin[s] >= lo && plan.bin[s] <= hi) order.push_back(s);
+        }
+    }
+  } else {
+    order.resize(S);
+    std::iota(order.begin(), order.end(), int64_t(0));
   }
   int64_t at = 0;
   for (int64_t s : order) {
@@ -312,6 +336,7 @@ qmk_status build_tables(qmk_ctx ctx, bool* relay) {
   std::vector<PrimDev> prim;
   std::vector<NucGroup> group;
   std::vector<int32_t> dev_of(ctx->nucl_num, -1);
+  std::vector<int64_t> order;
   NucGroup cur{0, 0, 0, 0, 0, 0, 0, 0};
   size_t smem = 0;
   auto close_group = [&]() {
@@ -353,10 +378,11 @@ qmk_status build_tables(qmk_ctx ctx, bool* relay) {
       sd.l = ctx->sh_l[s];
       sd.p_begin = static_cast<int32_t>(prim.size()) - cur.p_begin;
       // primitives of the shell by ascending exponent (Section 3.1)
-      std::vector<int64_t> order(ctx->sh_off[s + 1] - ctx->sh_off[s]);
+      auto narrower = [&](int64_t a, int64_t b) { return ctx->expo[a] < ctx->expo[b]; };
+      order.resize(ctx->sh_off[s + 1] - ctx->sh_off[s]);
       std::iota(order.begin(), order.end(), ctx->sh_off[s]);
-      std::stable_sort(order.begin(), order.end(),
-                       [&](int64_t a, int64_t b) { return ctx->expo[a] < ctx->expo[b]; });
+      if (!std::is_sorted(order.begin(), order.end(), narrower))
+        std::stable_sort(order.begin(), order.end(), narrower);
       for (int64_t k : order) {
         PrimDev pd{ctx->expo[k], ctx->coef[k] * ctx->pf[k] * ctx->sf[s]};
         prim.push_back(pd);
@@ -378,17 +404,6 @@ qmk_status build_tables(qmk_ctx ctx, bool* relay) {
   close_group();
   if (group.empty()) return fail(ctx, QMK_NOT_SET, "basis has no shells");
 
-  // earlier calls may still be reading the tables
-  const qmk_status ws = wait_own_work(ctx);
-  if (ws != QMK_OK) return ws;
-  auto up = [&](DevBuf& b, const void* src, size_t n) -> hipError_t {
-    hipError_t e = b.ensure(n);
-    if (e != hipSuccess) return e;
-    return hipMemcpy(b.p, src, n, hipMemcpyHostToDevice);
-  };
-  QMK_HIP(ctx, up(ctx->d_nuc, nuc.data(), nuc.size() * sizeof(NucDev)), "upload nuclei");
-  QMK_HIP(ctx, up(ctx->d_shell, shell.data(), shell.size() * sizeof(ShellDev)), "upload shells");
-  QMK_HIP(ctx, up(ctx->d_prim, prim.data(), prim.size() * sizeof(PrimDev)), "upload primitives");
   // the rows' AOs; copies of C (and what is derived from them) follow the rows
   const bool ordered = ctx->ao_num >= kOrderRowsAo;
   std::vector<int32_t> row_of(ordered ? ctx->ao_num : 0), ao_of(row_of.size());
@@ -409,15 +424,23 @@ qmk_status build_tables(qmk_ctx ctx, bool* relay) {
     ctx->row_of = row_of;
   }
   ctx->shell_row = row;
-  QMK_HIP(ctx, up(ctx->d_aofac, af.data(), af.size() * sizeof(double)), "upload M");
+  TableSet tables;
+  tables.add(ctx->d_nuc, nuc);
+  tables.add(ctx->d_shell, shell);
+  tables.add(ctx->d_prim, prim);
+  tables.add(ctx->d_aofac, af);
+  tables.add(ctx->d_group, group);
+  tables.add(ctx->d_devof, dev_of);
   if (ordered) {
-    QMK_HIP(ctx, up(ctx->d_ao_of, ao_of.data(), ao_of.size() * sizeof(int32_t)), "upload AO rows");
-    QMK_HIP(ctx, up(ctx->d_aofac_caller, ctx->af.data(), ctx->af.size() * sizeof(double)), "upload M");
-    QMK_HIP(ctx, up(ctx->d_shell_caller, shell_caller.data(), shell_caller.size() * sizeof(ShellDev)),
-            "upload shells");
+    tables.add(ctx->d_ao_of, ao_of);
+    tables.add(ctx->d_aofac_caller, ctx->af);
+    tables.add(ctx->d_shell_caller, shell_caller);
   }
-  QMK_HIP(ctx, up(ctx->d_group, group.data(), group.size() * sizeof(NucGroup)), "upload groups");
-  QMK_HIP(ctx, up(ctx->d_devof, dev_of.data(), dev_of.size() * sizeof(int32_t)), "upload map");
+  const qmk_status ws = wait_own_work(ctx);  // earlier calls may still be reading the tables
+  if (ws != QMK_OK) return ws;
+  QMK_HIP(ctx, tables.place(ctx->d_tables), "alloc tables");
+  QMK_HIP(ctx, hipMemcpy(ctx->d_tables.p, tables.bytes.data(), tables.bytes.size(), hipMemcpyHostToDevice),
+          "upload tables");
 
   ctx->n_groups = static_cast<int32_t>(group.size());
   ctx->nucl_dev = static_cast<int32_t>(nuc.size());
@@ -1159,6 +1182,7 @@ qmk_status qmk_set_basis(qmk_ctx ctx, int64_t shell_num, int64_t prim_num,
   ctx->ao_num = ao_num;
   ctx->has_basis = true;
   ctx->row_of.clear();  // until the tables are built
+  ctx->row_plan.ready = false;
   ctx->tables_dirty = true;
   ctx->coef_dirty = true;
   ++ctx->date;

@@ -2,9 +2,12 @@
 // the batch executor (batch.cpp).  Not part of the public ABI.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <functional>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/qmk.h"
@@ -42,6 +45,35 @@ struct DevBuf {
   }
   template <typename T>
   T* as() const { return static_cast<T*>(p); }
+};
+
+// A table inside one device buffer of tables.
+struct TabPtr {
+  void* p = nullptr;
+  template <typename T>
+  T* as() const { return static_cast<T*>(p); }
+};
+
+// Collects host tables, so that one copy uploads them all (a copy per table was a
+// launch and a gap on the stream for each of a batch's thirteen, and a blocking
+// call for each of a context's nine).
+struct TableSet {
+  std::vector<unsigned char> bytes;
+  std::vector<std::pair<TabPtr*, size_t>> at;
+  template <typename T>
+  void add(TabPtr& t, const std::vector<T>& v) {
+    const size_t off = (bytes.size() + 255) / 256 * 256;
+    bytes.resize(off + std::max<size_t>(v.size() * sizeof(T), 16));
+    if (!v.empty()) std::memcpy(bytes.data() + off, v.data(), v.size() * sizeof(T));
+    at.push_back({&t, off});
+  }
+  // Gives every table its place in b; `bytes` is then to be copied there.
+  hipError_t place(DevBuf& b) {
+    const hipError_t e = b.ensure(bytes.size());
+    if (e != hipSuccess) return e;
+    for (auto& a : at) a.first->p = static_cast<unsigned char*>(b.p) + a.second;
+    return hipSuccess;
+  }
 };
 
 struct DeviceGuard {
@@ -91,7 +123,8 @@ struct qmk_ctx_s {
 
   // device tables
   bool tables_dirty = true;
-  DevBuf d_nuc, d_shell, d_prim, d_aofac, d_group, d_devof;
+  DevBuf d_tables;
+  qmk::TabPtr d_nuc, d_shell, d_prim, d_aofac, d_group, d_devof;
   qmk::AoTables tab{};
   // Rows of the context's own AO arrays (and of every copy of C and of Gbar):
   // row_of[k] of the caller's AO k, and its inverse on the device; empty where
@@ -99,7 +132,15 @@ struct qmk_ctx_s {
   // caller's rows (AO values for the caller, cusp tables).
   std::vector<int64_t> shell_row;  // first row of every shell
   std::vector<int32_t> row_of;
-  DevBuf d_ao_of, d_shell_caller, d_aofac_caller;
+  qmk::TabPtr d_ao_of, d_shell_caller, d_aofac_caller;
+  // what the order of rows takes from the basis alone (order_rows)
+  struct RowPlan {
+    bool ready = false;
+    std::vector<int32_t> bin;        // of every shell: its smallest exponent's
+    std::vector<int64_t> of_nucleus, first;  // shells of nucleus A, the widest first: of_nucleus[first[A]] ...
+    std::vector<int32_t> used;       // bins with shells, ascending
+    std::vector<double> rows, reach; // of every used bin: AOs, farthest reach
+  } row_plan;
   qmk::AoTables tab_caller{};
   const int32_t* ao_of() const { return row_of.empty() ? nullptr : d_ao_of.as<int32_t>(); }
   int32_t n_groups = 0, nucl_dev = 0;
