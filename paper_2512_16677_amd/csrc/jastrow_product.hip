@@ -236,13 +236,18 @@ __device__ __forceinline__ void een_tile_body(const JasArgs& g, int64_t w, int m
 }
 
 template <int NORD, int WGM, int WGN, int TM, int TN>
-__global__ __launch_bounds__(64 * WGM * WGN, 3) void een_product_kernel(JasArgs g, int nM, int nN, int64_t slots) {
+__global__ __launch_bounds__(64 * WGM * WGN, 3) void een_product_kernel(JasArgs g, int nM, int nN, int64_t slots,
+                                                                        int64_t full) {
   constexpr int NG = kNumGroups<NORD>, LDS = een_lds<NORD, WGM, WGN, TM, TN>();
   static_assert(LDS * 8 <= 160 * 1024, "LDS");
   __shared__ __align__(16) double sm[LDS];
-  // all tiles of a walker on one XCD: they share its operands
-  const int tiles = NG * nM * nN, x = blockIdx.x & 7, r = blockIdx.x >> 3;
-  const int64_t w = static_cast<int64_t>(r / tiles) * 8 + x;
+  // The first `full` walkers go eight at a time to the eight XCDs, all tiles of one
+  // walker to one XCD, because they share its operands; the tiles of the others
+  // are dealt out over all XCDs (see run_een).
+  const int tiles = NG * nM * nN;
+  const int64_t rest = static_cast<int64_t>(blockIdx.x) - full * tiles;
+  const int x = blockIdx.x & 7, r = rest < 0 ? static_cast<int>(blockIdx.x >> 3) : static_cast<int>(rest);
+  const int64_t w = rest < 0 ? static_cast<int64_t>(r / tiles) * 8 + x : full + r / tiles;
   if (w >= g.nw) return;
   const int t = r - r / tiles * tiles, gr = t / (nM * nN), u = t - gr * (nM * nN), mt = u % nM, nt = u / nM;
   double* const part = g.part + w * g.part_ld + gr * slots;
@@ -285,14 +290,25 @@ template <int NORD>
 hipError_t run_een(int cfg, const JasArgs& g, hipStream_t s) {
   const TileCfg t = kJasTiles[cfg];
   const int64_t nM = (g.nn + t.bm() - 1) / t.bm(), nN = (g.ne + t.bn() - 1) / t.bn();
-  const int64_t blocks = (g.nw + 7) / 8 * 8 * nM * nN * kNumGroups<NORD>;
+  const int64_t tiles = nM * nN * kNumGroups<NORD>;
+  // Where few walkers are left over after whole rounds of eight, their tiles are
+  // dealt out over all XCDs, some of which would idle: up to three of them, or
+  // six of many tiles.  With more, sharing the operands in one L2 is worth more.
+  // Whole call, order 5, one XCD per walker / dealt out: 300 nuclei x 1050 electrons,
+  // 1 walker 549 / 248 us, 5 walkers 596 / 473, 7 walkers 609 / 628; 80 x 280, 3 walkers
+  // 74 / 74, 5 walkers 77 / 81, 20 walkers (4 left) 110 / 103; 1000 x 3000, 1 walker
+  // 9280 / 1721.
+  const int64_t left = g.nw & 7;
+  const bool deal = left <= 3 || (left <= 6 && tiles >= 1024);
+  const int64_t full = deal ? g.nw - left : (g.nw + 7) / 8 * 8;
+  const int64_t blocks = (deal ? g.nw : full) * tiles;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(blocks));
   switch (cfg) {
 #define QMK_JAS_CASE(id, wgm, wgn, tm, tn)                                                                    \
   case id:                                                                                                    \
     hipLaunchKernelGGL((een_product_kernel<NORD, wgm, wgn, tm, tn>), grid, dim3(64 * wgm * wgn), 0, s, g,     \
-                       static_cast<int>(nM), static_cast<int>(nN), een_slots(cfg, g.nn, g.ne));               \
+                       static_cast<int>(nM), static_cast<int>(nN), een_slots(cfg, g.nn, g.ne), full);         \
     break;
     QMK_JAS_TILES(QMK_JAS_CASE)
 #undef QMK_JAS_CASE
