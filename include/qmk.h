@@ -285,10 +285,10 @@ qmk_status qmk_get_screening_density(qmk_ctx ctx, double* active_fraction);
  *   det  device FP64 [batch]
  *   adj  device FP64 [batch][n][n], adj(A) = transpose of the cofactor matrix
  * 1 <= n <= 4: explicit cofactors (exact also for singular matrices).
- * 5 <= n <= 32: LU with partial pivoting, adj = det * A^{-1}; when the
- * factorisation meets an exactly zero pivot, det = 0 and the adjugate is
- * the rank-one cofactor matrix built from the null vectors of the
- * triangular factor (one zero pivot) or zero (two or more).  batch = 0 does nothing
+ * 5 <= n <= 32: elimination with partial pivoting, adj = det * A^{-1}; a
+ * matrix that eliminates to exact zeros in a column has det = 0 and as adjugate
+ * the rank-one cofactor matrix built from its null vectors (one such column)
+ * or zero (two or more).  batch = 0 does nothing
  * (the pointers may then be NULL).  Runs on the context's device and the
  * given stream; uses no other context state. */
 qmk_status qmk_det_adj(qmk_ctx ctx, int64_t n, int64_t batch, const double* a, double* det, double* adj,

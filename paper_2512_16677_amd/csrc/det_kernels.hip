@@ -7,9 +7,11 @@
 // stores); the n*n entries live in registers and every
 // cofactor is an unrolled signed minor determinant (Laplace expansion along
 // the first row, compile-time n), so the result is exact also for singular
-// matrices.  5 <= n <= 32: one wavefront per matrix, LU with partial
-// pivoting in LDS (lanes over rows), det = sign * prod(U_kk), and
-// adj = det * A^{-1} from substitutions (lanes over columns of A^{-1}).
+// matrices.  5 <= n <= 32: two to eight matrices per wavefront, Gauss-Jordan
+// elimination with partial pivoting and a row per lane in registers,
+// det = sign * product of the pivots, adj = det * A^{-1}; a wavefront with a
+// pivot or determinant outside the normal numbers takes a second pass over its
+// matrices, which also knows singular ones.
 #include <type_traits>
 
 #include "qmk_internal.h"
@@ -105,167 +107,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS of one wavefront for the LU of one N x N matrix and the solves.
-template <int N>
-struct LuLds {
-  double lu[N][33];
-  double x[N][33];  // column `lane` of A^{-1}
-  double a[N], r[N];
-  int piv[N];
-};
-
-// One matrix by the whole wavefront: LU with partial pivoting in LDS (lanes
-// over rows), adj = det * A^{-1} from substitutions (lanes over columns), and
-// the singular cases.
-template <int N>
-__device__ void lu_general(const double* __restrict__ src, double* __restrict__ det, double* __restrict__ dst,
-                           int lane, LuLds<N>& L) {
-  double(*lu)[33] = L.lu;
-  wave_lds_sync();  // the LDS is shared with the caller's staging
-#pragma unroll 1
-  for (int e = lane; e < N * N; e += 64) lu[e / N][e % N] = src[e];
-  wave_lds_sync();
-  double sign = 1.0, d = 1.0;
-#pragma unroll 1
-  for (int k = 0; k < N; ++k) {
-    // pivot: largest |a_ik|, i >= k (ties to the lowest row)
-    double v = lane >= k && lane < N ? fabs(lu[lane][k]) : -1.0;
-    int idx = lane;
-#pragma unroll 1
-    for (int off = 32; off > 0; off >>= 1) {
-      const double ov = __shfl_xor(v, off, 64);
-      const int oi = __shfl_xor(idx, off, 64);
-      if (ov > v || (ov == v && oi < idx)) {
-        v = ov;
-        idx = oi;
-      }
-    }
-    // (with NaN entries the lanes may disagree: one of them decides, and where
-    // it knows of no row but NaN ones, row k stays)
-    int p = __builtin_amdgcn_readfirstlane(idx);
-    if (p < k || p >= N) p = k;
-    if (lane == 0) L.piv[k] = p;
-    if (p != k) {
-      if (lane < N) {
-        const double t = lu[k][lane];
-        lu[k][lane] = lu[p][lane];
-        lu[p][lane] = t;
-      }
-      sign = -sign;
-    }
-    wave_lds_sync();
-    const double piv = lu[k][k];
-    d *= piv;
-    if (lane > k && lane < N) {
-      // a zero pivot leaves only zeros below it: nothing to eliminate
-      const double l = piv != 0.0 ? lu[lane][k] / piv : 0.0;
-      lu[lane][k] = l;
-#pragma unroll 1
-      for (int j = k + 1; j < N; ++j) lu[lane][j] -= l * lu[k][j];
-    }
-    wave_lds_sync();
-  }
-  d *= sign;
-  if (lane == 0) *det = d;
-  // Exactly zero pivots make d A^{-1} undefined; the adjugate is still the
-  // transposed cofactor matrix.  With PA = LU, adj(A) = adj(U) L^{-1} sign P.
-  // Two or more zero pivots (rank <= n - 2): adj(A) = 0.  One, at k0 (rank
-  // n - 1): adj(U) = c a b^T with c = prod_{m != k0} u_mm (the (k0, k0)
-  // cofactor), U a = 0, a_k0 = 1, a_m = 0 past k0, and b^T U = 0, b_k0 = 1,
-  // b_m = 0 before k0; so adj(A) = sign c a r^T with r = P^T L^{-T} b.
-  int nzero = 0, k0 = -1;
-#pragma unroll 1
-  for (int m = 0; m < N; ++m)
-    if (lu[m][m] == 0.0) {
-      ++nzero;
-      k0 = m;
-    }
-  if (nzero > 0) {
-    if (nzero >= 2) {
-#pragma unroll 1
-      for (int e = lane; e < N * N; e += 64) dst[e] = 0.0;
-      return;
-    }
-    if (lane == 0) {
-      double c = sign;
-#pragma unroll 1
-      for (int m = 0; m < N; ++m)
-        if (m != k0) c *= lu[m][m];
-      double* a = L.a;
-      double* r = L.r;
-#pragma unroll 1
-      for (int m = N - 1; m >= 0; --m) {
-        if (m >= k0) {
-          a[m] = m == k0 ? 1.0 : 0.0;
-        } else {
-          double t = 0.0;
-#pragma unroll 1
-          for (int q = m + 1; q <= k0; ++q) t += lu[m][q] * a[q];
-          a[m] = -t / lu[m][m];
-        }
-      }
-      // b into r, then z = L^{-T} b in place (L unit lower, below the diagonal of lu)
-#pragma unroll 1
-      for (int j = 0; j < N; ++j) {
-        if (j <= k0) {
-          r[j] = j == k0 ? 1.0 : 0.0;
-        } else {
-          double t = 0.0;
-#pragma unroll 1
-          for (int q = k0; q < j; ++q) t += r[q] * lu[q][j];
-          r[j] = -t / lu[j][j];
-        }
-      }
-#pragma unroll 1
-      for (int i = N - 1; i >= 0; --i)
-#pragma unroll 1
-        for (int j = i + 1; j < N; ++j) r[i] -= lu[j][i] * r[j];
-      // r = P^T z: the row swaps undone in reverse order
-#pragma unroll 1
-      for (int k = N - 1; k >= 0; --k) {
-        const int p = L.piv[k];
-        const double t = r[k];
-        r[k] = r[p];
-        r[p] = t;
-      }
-#pragma unroll 1
-      for (int m = 0; m < N; ++m) a[m] *= c;
-    }
-    wave_lds_sync();
-    if (lane < N)
-#pragma unroll 1
-      for (int i = 0; i < N; ++i) dst[i * N + lane] = L.a[i] * L.r[lane];
-    return;
-  }
-  // column `lane` of A^{-1}: solve L U x = P e_lane
-  if (lane < N) {
-    // P e_lane: the row permutation applied to the identity
-    int col = lane;
-#pragma unroll 1
-    for (int k = 0; k < N; ++k) {
-      const int p = L.piv[k];
-      if (col == k) col = p;
-      else if (col == p) col = k;
-    }
-#pragma unroll 1
-    for (int i = 0; i < N; ++i) {
-      double t = i == col ? 1.0 : 0.0;
-#pragma unroll 1
-      for (int j = 0; j < i; ++j) t -= lu[i][j] * L.x[j][lane];
-      L.x[i][lane] = t;
-    }
-#pragma unroll 1
-    for (int i = N - 1; i >= 0; --i) {
-      double t = L.x[i][lane];
-#pragma unroll 1
-      for (int j = i + 1; j < N; ++j) t -= lu[i][j] * L.x[j][lane];
-      t /= lu[i][i];
-      L.x[i][lane] = t;
-      dst[i * N + lane] = d * t;
-    }
-  }
-}
-
 // Largest v of each group of G consecutive lanes (8, 16 or 32), in every lane.
 template <int G>
 __device__ __forceinline__ double group_max(double v) {
@@ -295,9 +136,11 @@ __device__ __forceinline__ double group_max(double v) {
 // is always register 0.  One
 // wavefront per matrix with the LU in LDS ran N serial steps with N of 64
 // lanes busy and kept the solutions in scratch memory.
-// 50,000 matrices of N = 16: 1092 us before, 80 us now (2.6 TB/s);
-// N = 5, 8, 24 and 32 in as many bytes 1484, 1134, 1165 and 1326 us before, 59,
-// 48, 139 and 155 us now.
+// 50,000 matrices of N = 16: 1082 us before, 76 us now (2.7 TB/s); N = 5, 8 and 24 166,
+// 310 and 2552 us before, 13, 20 and 278 us now; 20,000 of N = 32 1991 and 214 us.
+// Singular ones (a zero row) of N = 8, 16, 24 and 32: 233, 603, 1147 and 779 us before,
+// 34, 151, 593 and 484 us now (the wavefront's LU one matrix after another took
+// 312, 942, 1731 and 1485 us).
 template <int N>
 __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_gj_kernel(const double* __restrict__ A,
                                                                           int64_t batch,
@@ -308,7 +151,6 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
   constexpr int RP = (N + 1) / 2 + 1;  // pitch of the groups' pivot rows, in pairs of columns
   union alignas(16) Lds {
     double m[NM][N][LD];
-    LuLds<N> lu;
     double2 row[NM][RP];
   };
   __shared__ Lds s_lds[4];
@@ -319,10 +161,13 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
   const int nb = static_cast<int>(min<int64_t>(NM, batch - b0));
   double* const sm = &s_lds[w].m[0][0][0];
   const double* const src = A + b0 * E;
+  double* const dst = adj + b0 * E;
+  const int gi = lane / G, i = lane % G, base = lane - i;
+  double a[N];
+  constexpr int Q = (NM * E + 63) / 64;
   // the wavefront's matrices are contiguous: coalesced loads, all in flight
   // before the first is stored, rows padded in LDS (past the last matrix: its
   // last element again)
-  constexpr int Q = (NM * E + 63) / 64;
   {
     double in[Q];
 #pragma unroll
@@ -334,15 +179,30 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
     }
   }
   wave_lds_sync();
-  const int gi = lane / G, i = lane % G, base = lane - i;
-  double a[N];
+  auto take_rows = [&]() {
 #pragma unroll
-  for (int j = 0; j < N; ++j) a[j] = i < N ? sm[(gi * N + i) * LD + j] : 0.0;
+    for (int j = 0; j < N; ++j) a[j] = i < N ? sm[(gi * N + i) * LD + j] : 0.0;
+    wave_lds_sync();  // the rows are read; the pivot rows take their place
+  };
+  double2* const row = &s_lds[w].row[0][0] + gi * RP;
+  auto put_row = [&]() {  // two columns per access
+#pragma unroll
+    for (int j = 0; j < (N + 1) / 2; ++j) row[j] = double2{a[2 * j], 2 * j + 1 < N ? a[2 * j + 1] : 0.0};
+  };
+  double r[2 * ((N + 1) / 2)];
+  auto get_row = [&]() {
+#pragma unroll
+    for (int j = 0; j < (N + 1) / 2; ++j) {
+      const double2 v2 = row[j];
+      r[2 * j] = v2.x;
+      r[2 * j + 1] = v2.y;
+    }
+  };
+  constexpr uint32_t kAll = N == 32 ? ~0u : (1u << (N & 31)) - 1u;
 
-  wave_lds_sync();  // the rows are read; the pivot rows take their place
-  double2* const s_row = &s_lds[w].row[0][0];
+  take_rows();
   double d = 1.0, my_piv = 1.0;
-  uint32_t unused = N == 32 ? ~0u : (1u << (N & 31)) - 1u;  // rows not yet a pivot row
+  uint32_t unused = kAll;  // rows not yet a pivot row
   int my_k = 0, odd = 0;
   bool bad = false;
 #pragma unroll(N % 2 == 0 ? 2 : 1)
@@ -359,22 +219,11 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
     odd ^= __builtin_popcount(unused & ((1u << p) - 1u)) & 1;
     unused &= ~(1u << p);
     const bool own = i == p;
-    // the pivot row goes to its group through LDS, two columns per access
-    double2* const row = s_row + gi * RP;
-    if (own) {
-#pragma unroll
-      for (int j = 0; j < (N + 1) / 2; ++j) row[j] = double2{a[2 * j], 2 * j + 1 < N ? a[2 * j + 1] : 0.0};
-    }
+    // the pivot row goes to its group through LDS
+    if (own) put_row();
     wave_lds_sync();
-    double r[2 * ((N + 1) / 2)];
-#pragma unroll
-    for (int j = 0; j < (N + 1) / 2; ++j) {
-      const double2 v2 = row[j];
-      r[2 * j] = v2.x;
-      r[2 * j + 1] = v2.y;
-    }
+    get_row();
     const double piv = r[0];
-    bad = bad || !(fabs(piv) >= 2.2250738585072014e-308);
     d *= piv;
     if (own) {
       my_k = k;
@@ -390,7 +239,11 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
     wave_lds_sync();  // the row is read before the next one is written
   }
   if (odd) d = -d;
-  bad = bad || !(fabs(d) <= 1.7976931348623157e308);
+  // every lane looks at its own pivot
+  const bool normal = fabs(my_piv) >= 0x1p-1022 && fabs(my_piv) <= 0x1p+1022;
+  const uint64_t odd_pivots = __ballot(i < N && !normal) >> base;
+  bad = bad || (odd_pivots & (G == 32 ? 0xffffffffu : (1u << (G & 31)) - 1u)) != 0 ||
+        !(fabs(d) <= 1.7976931348623157e308);
 
   // A^{-1}[k of row i][p_k] = a[k] / pivot of row i
   wave_lds_sync();
@@ -400,21 +253,120 @@ __global__ __launch_bounds__(256, N <= 14 ? 4 : (N <= 24 ? 3 : 2)) void det_adj_
     for (int k = 0; k < N; ++k) sm[(gi * N + my_k) * LD + s_piv[w][gi][k]] = d * (a[k] * inv);
   }
   wave_lds_sync();
-  double* const dst = adj + b0 * E;
-  // matrices that need the general path are left to it (it reads them again)
-  const uint64_t again = __ballot(bad);
+  const uint64_t again = __ballot(bad && gi < nb);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int e = q * 64 + lane;
     if (e < nb * E && (again == 0 || !((again >> (e / E * G)) & 1u))) dst[e] = sm[e / N * LD + e % N];
   }
   if (i == 0 && gi < nb && !bad) det[b0 + gi] = d;
-  if (again != 0) {
-    for (int m = 0; m < nb; ++m) {
-      if (!((again >> (m * G)) & 1u)) continue;
-      lu_general<N>(src + m * E, det + b0 + m, dst + m * E, lane, s_lds[w].lu);
+  if (again == 0) return;
+
+  // Second pass for the wavefront's matrices that met a pivot that is zero,
+  // NaN, or so small or large that its reciprocal is not a normal number, or
+  // whose determinant is not finite: the same elimination, which multiplies a row by
+  // the other rows' pivots instead of dividing det by its own, takes a row with a NaN where no other has an entry, and passes over a column
+  // that is zero in every unused row.  One column k0 passed over (rank N - 1)
+  // leaves one row p0 = t^T A of zeros, t its coefficients of the identity, and
+  // the null vector x: x_k0 = 1, x_k = -(column k0 of the row of pivot k) / pivot k.
+  // Then adj(A) = c x t^T with c the cofactor of (p0, k0), the signed product of
+  // the pivots; with two or more adj(A) = 0.
+  wave_lds_sync();
+#pragma unroll 1
+  for (int e = lane; e < NM * E; e += 64) sm[e / N * LD + e % N] = src[min(e, nb * E - 1)];
+  wave_lds_sync();
+  take_rows();
+  d = 1.0;
+  my_piv = 1.0;
+  unused = kAll;
+  my_k = odd = 0;
+  double rest = 1.0;  // product of the pivots but this lane's
+  int passed = 0, k0 = 0;
+#pragma unroll 1
+  for (int k = 0; k < N; ++k) {
+    const bool cand = (unused >> i) & 1u;
+    const double v = cand ? fabs(a[0]) : -1.0;
+    const double vm = group_max<G>(v);
+    const uint64_t hit = __ballot(cand && v == vm);
+    const uint32_t mine = static_cast<uint32_t>(hit >> base) & (G == 32 ? ~0u : (1u << (G & 31)) - 1u);
+    const uint64_t nan = __ballot(cand && v != v);
+    const uint32_t nans = static_cast<uint32_t>(nan >> base) & (G == 32 ? ~0u : (1u << (G & 31)) - 1u);
+    const bool none = vm == 0.0 && nans == 0;
+    // (fewer rows than steps are used, so that one is left; NaNs beat zeros)
+    const int p = __builtin_ctz(vm > 0.0 || nans == 0 ? mine : nans);
+    const bool own = !none && i == p;
+    if (none) {
+      ++passed;
+      k0 = k;
+    } else {
+      odd ^= __builtin_popcount(unused & ((1u << p) - 1u)) & 1;
+      unused &= ~(1u << p);
+    }
+    if (own) put_row();
+    wave_lds_sync();
+    get_row();
+    const double piv = none ? 1.0 : r[0];
+    d *= piv;
+    if (own) {
+      my_k = k;
+      my_piv = piv;
+    } else {
+      rest *= piv;
+    }
+    if (i == 0) s_piv[w][gi][k] = p;
+    const double a0 = a[0], f = own || none ? 0.0 : a0 / piv;
+#pragma unroll
+    for (int j = 1; j < N; ++j) a[j - 1] = own || none ? a[j] : fma(-f, r[j], a[j]);
+    a[N - 1] = none ? a0 : (own ? 1.0 : -f);
+    wave_lds_sync();
+  }
+  const int p0 = unused ? __builtin_ctz(unused) : 0;
+  // (the order of the pivot rows has p0 at k0, not after the rows of later steps)
+  if ((odd + (passed ? N - 1 - k0 : 0)) & 1) {
+    d = -d;
+    rest = -rest;
+  }
+  if (d != d) rest = d;
+  // x and t take the places of rows 0 and 1, and the results those of all rows
+  // once they are read
+  double* const x = sm + gi * N * LD;
+  double* const t = x + LD;
+  wave_lds_sync();
+  if (passed == 1 && i < N) {
+    if (i == p0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (k != k0) t[s_piv[w][gi][k]] = a[k];
+      t[p0] = 1.0;
+      x[k0] = 1.0;
+    } else {
+      double c = 0.0;
+#pragma unroll
+      for (int k = 0; k < N; ++k) c = k == k0 ? a[k] : c;
+      x[my_k] = -c / my_piv;
     }
   }
+  wave_lds_sync();
+  if (passed == 1) {
+    const double xi = i < N ? d * x[i] : 0.0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) a[j] = xi * t[j];
+  }
+  wave_lds_sync();
+  if (i < N) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      if (passed == 0)
+        sm[(gi * N + my_k) * LD + s_piv[w][gi][k]] = rest * a[k];
+      else
+        sm[(gi * N + i) * LD + k] = passed == 1 ? a[k] : 0.0;
+    }
+  }
+  wave_lds_sync();
+#pragma unroll 1
+  for (int e = lane; e < nb * E; e += 64)
+    if ((again >> (e / E * G)) & 1u) dst[e] = sm[e / N * LD + e % N];
+  if (i == 0 && gi < nb && bad) det[b0 + gi] = passed ? d * 0.0 : d;
 }
 
 template <int N>
