@@ -1385,8 +1385,10 @@ qmk_status qmk_jastrow_een(qmk_ctx ctx, int64_t nord, double kappa, int64_t n_te
   }
   // the product (k, m >= 1) needs m <= (nord - 1) / 2
   const int mk = static_cast<int>((nord - 1) / 2);
-  // electrons j of both operands padded to whole steps, their rows to 16
-  const int64_t jp = round_up(ne, 16), nnp = round_up(nn, 16), lda = std::max(mk, 1) * nnp, ldb = round_up(ne, 16);
+  // electrons j of both operands padded to whole steps; their rows to whole cache
+  // lines, or, where that would be much of a short row, to the 16 bytes of a load
+  auto row_pad = [](int64_t n) { return round_up(n, n >= 64 ? 16 : 2); };
+  const int64_t jp = round_up(ne, 16), nnp = row_pad(nn), lda = std::max(mk, 1) * nnp, ldb = row_pad(ne);
   QMK_HIP(ctx, ctx->een_ra.ensure(static_cast<size_t>(nw * jp * lda) * 8), "alloc rescaled e-n powers");
   QMK_HIP(ctx, ctx->een_x.ensure(static_cast<size_t>(P * nn) * 8), "alloc rescaled e-n distances");
   QMK_HIP(ctx, ctx->een_rt.ensure(static_cast<size_t>(nw * jp * ldb) * 8), "alloc rescaled e-e distances");

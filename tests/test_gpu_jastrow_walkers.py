@@ -34,3 +34,27 @@ def test_numbers_of_walkers(nn, ne, walkers):
         assert np.all(np.abs(j[:m] - ref[:m]) <= 1e-12 * ref_abs[:m]), n
         assert np.array_equal(j, every[:n]), n
     ctx.close()
+
+
+def test_workspace_of_small_molecules():
+    """Rows of two electrons and two nuclei are not padded to cache lines: the
+    arrays of a walker hold about 130 doubles (800 in padded rows)."""
+    import paper_2512_16677_amd as q
+    n = 200000
+    elec = np.random.default_rng(0).normal(size=(n, 2, 3))
+    nucl = np.array([[0.0, 0.0, -0.7], [0.0, 0.0, 0.7]])
+    c = np.ones((q.jastrow_een_terms(5), 2))
+    ctx = q.Context()
+    ctx.set_nucleus(nucl)
+    ctx.set_point(elec)
+    out = torch.empty(n, dtype=torch.float64, device="cuda")
+    ctx.set_tile("jastrow_p", 0)
+    ctx.det_adj(torch.eye(5, dtype=torch.float64, device="cuda"))  # the library is loaded
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    j = ctx.jastrow_een(5, 0.8, c, out=out)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] <= 2048 * n
+    ref = oracle.jastrow_een(elec[:50], nucl, 0.8, 5, c)
+    assert np.all(np.abs(j.cpu().numpy()[:50] - ref) <= 1e-12 * oracle.jastrow_een(elec[:50], nucl, 0.8, 5, np.abs(c)))
+    ctx.close()
