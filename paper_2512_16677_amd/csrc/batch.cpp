@@ -476,12 +476,16 @@ qmk_status choose_batch_tile(qmk_batch b, GemmKind kind, hipStream_t s) {
       const qmk_status st = set_batch_items(b, kind, tiles, s);
       if (st != QMK_OK) return st;
       auto run = [&]() { return launch_batch_gemm(b, kind, tiles, b->g_first[k], b->g_items[k].size(), s); };
-      QMK_BHIP(b, run(), "tile trial");
-      QMK_BHIP(b, hipEventRecord(e0, s), "event");
-      QMK_BHIP(b, run(), "tile trial");
-      QMK_BHIP(b, hipEventRecord(e1, s), "event");
-      QMK_BHIP(b, hipEventSynchronize(e1), "tile trial");
-      (void)hipEventElapsedTime(ms, e0, e1);
+      // a warm-up, which long products are timed in too, and one more
+      for (int rep = 0; rep < 2; ++rep) {
+        QMK_BHIP(b, hipEventRecord(e0, s), "event");
+        QMK_BHIP(b, run(), "tile trial");
+        if (rep == 0 && best_ms <= kLongTrialMs) continue;
+        QMK_BHIP(b, hipEventRecord(e1, s), "event");
+        QMK_BHIP(b, hipEventSynchronize(e1), "tile trial");
+        (void)hipEventElapsedTime(ms, e0, e1);
+        if (trial_lost(*ms, best_ms, rep == 0)) return QMK_OK;
+      }
       if (best_ms < 0.0f || *ms < best_ms) {
         best_ms = *ms;
         best = tiles;

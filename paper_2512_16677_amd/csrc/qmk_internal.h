@@ -394,6 +394,12 @@ struct GemmProblem {
 // its own).
 int num_tiles(GemmKind kind, Prec prec);
 bool tile_feasible(Prec prec, int cfg);
+// True if a tile that took ms (as its warm-up, or after it) need not be run again
+// to lose against best_ms (< 0: none yet).  Only products long enough that a first
+// run says what the next will.  First gradient of a new size, 605 / 1205 AOs in
+// FP64: 12 tiles run three times 99 / 390 ms, 16 tiles 127 / 496 ms, 74 / 270 ms so.
+constexpr float kLongTrialMs = 0.3f;
+bool trial_lost(float ms, float best_ms, bool warm_up);
 int default_tile(const GemmProblem& p);
 // Returns the tile for p, timing every feasible tile through `enqueue` on
 // stream s the first time p is seen.  *err receives a HIP error, if any.

@@ -3,7 +3,8 @@
 // For every distinct product (kind, precision, operand types, M, N, L) the
 // first call times each tile shape of the kernel's table on the caller's own
 // operands (one warm-up launch, then the best of two timed launches with HIP
-// events on the caller's stream) and remembers the fastest.  Later calls --
+// events on the caller's stream; fewer for a tile that cannot win any more) and
+// remembers the fastest.  Later calls --
 // including calls from other contexts -- reuse the choice.  The table of
 // choices can be persisted: QMK_TUNE_CACHE=<file> loads it at first use and
 // rewrites it after each new decision (a flat JSON object key -> tile id).
@@ -124,6 +125,10 @@ bool usable(const GemmProblem& p, int cfg) {
 }
 }  // namespace
 
+bool trial_lost(float ms, float best_ms, bool warm_up) {
+  return best_ms > kLongTrialMs && ms > best_ms * (warm_up ? 1.1f : 1.03f);
+}
+
 int default_tile(const GemmProblem& p) {
   int best = -1;
   double best_cost = 0.0;
@@ -162,12 +167,10 @@ int choose_tile(const GemmProblem& p, int device, hipStream_t s,
     float best_ms = -1.0f;
     for (int c = 0; c < num_tiles(p.kind, p.prec); ++c) {
       if (!usable(p, c)) continue;
-      hipError_t e = enqueue(c);  // warm-up
-      if (e != hipSuccess) continue;
       float t_min = -1.0f;
-      for (int rep = 0; rep < 2; ++rep) {
+      for (int rep = 0; rep < 3; ++rep) {  // a warm-up and two more
         (void)hipEventRecord(a, s);
-        e = enqueue(c);
+        hipError_t e = enqueue(c);
         (void)hipEventRecord(b, s);
         if (e != hipSuccess) break;
         if ((e = hipEventSynchronize(b)) != hipSuccess) {
@@ -176,7 +179,8 @@ int choose_tile(const GemmProblem& p, int device, hipStream_t s,
         }
         float ms = 0.0f;
         (void)hipEventElapsedTime(&ms, a, b);
-        if (t_min < 0.0f || ms < t_min) t_min = ms;
+        if (trial_lost(ms, best_ms, rep == 0)) break;
+        if (rep > 0 && (t_min < 0.0f || ms < t_min)) t_min = ms;
       }
       if (*err != hipSuccess) break;
       if (t_min >= 0.0f && (best_ms < 0.0f || t_min < best_ms)) {
