@@ -658,7 +658,7 @@ def main_large(a):
 
 def main_det(a):
     """Determinant + adjugate of 2^24 random n x n matrices, n = 2, 3, 4, and
-    2^16 matrices of n = 16 (LU path); one launch per step."""
+    2^16 matrices of n = 16 (elimination); one launch per step."""
     import torch
     import paper_2512_16677_amd as qmk
     ctx = qmk.Context()
@@ -692,7 +692,7 @@ def main_det(a):
             "unit": "matrices/s", "n_gpus": 1, "steps": a.steps, "warmup": a.warmup,
             "ms_per_step": d4["avg_ms"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
             "dtype": "f64", "data": "synthetic",
-            "config": {"workload": "2^24 random 4x4 FP64 matrices (also n = 2, 3; n = 16 by LU)"},
+            "config": {"workload": "2^24 random 4x4 FP64 matrices (also n = 2, 3; n = 16 by elimination)"},
             "roofline": {"bound": "hbm", "achieved": d4["GBps"], "peak": PEAKS["hbm_GBps"], "unit": "GB/s",
                          "frac": d4["GBps"] / PEAKS["hbm_GBps"], "traffic": None, "kernel": "det_adj_small<4>"},
             "sizes": res}

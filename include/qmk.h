@@ -302,10 +302,10 @@ qmk_status qmk_det_adj(qmk_ctx ctx, int64_t n, int64_t batch, const double* a, d
  * context's nuclei and points (walk_num walkers of elec_num electrons; the
  * basis is not needed).  Terms t run over p = 2..nord, k = 0..p-1,
  * l = 0..p-k-2 delta(k,0), each ascending, keeping those with p-k-l even
- * (qmk_jastrow_een_terms gives the count).  The P^{k,m} with m >= 1 are one
- * MFMA product per walker and k whose epilogue applies the coefficients, so
- * P is never stored; the m = 0 terms use the nucleus-independent row sums
- * of rt^k.  c: host FP64 [n_terms][nucl_num]; j_een: device FP64
+ * (qmk_jastrow_een_terms gives the count).  The P^{k,m} with k, m >= 1 that some
+ * term uses are MFMA products whose epilogue applies the coefficients, so P is
+ * never stored; the m = 0 terms use the nucleus-independent row sums of rt^k,
+ * the k = 0 terms sums over the electrons of each nucleus.  c: host FP64 [n_terms][nucl_num]; j_een: device FP64
  * [walk_num], overwritten.  2 <= nord <= 8, kappa > 0.  FP64 in every
  * precision mode; deterministic.  Errors: QMK_INVALID_ARG_BASE + 2/3/4 for
  * nord, kappa, n_terms; + 5 NULL c; + 6 j_een not device memory;
@@ -383,7 +383,10 @@ qmk_status qmk_get_timing(qmk_ctx ctx, int32_t kernel_class, double* total_ms, i
  * QMK_TUNE=0 picks by least padded work without timing).  qmk_set_tile
  * forces tile `tile` (0 .. count-1) for one product class of this context,
  * or restores the autotuned choice with -1; every tile gives the same
- * result up to rounding. */
+ * result up to rounding.  qmk_get_tile_count counts the tiles of the dense
+ * products in the context's precision mode.  The Jastrow product has a table of
+ * its own, with fewer tiles; it takes the numbers of the FP64 products, and those
+ * past its end start again from its first tile. */
 qmk_status qmk_get_tile_count(qmk_ctx ctx, int32_t* count);
 qmk_status qmk_set_tile(qmk_ctx ctx, int32_t kernel_class, int32_t tile);
 

@@ -314,7 +314,8 @@ class Context:
 
     def set_tile(self, kernel: str, tile: int):
         """Force MFMA tile `tile` for kernel class 'mo', 'gbar', 'dcoef', 'density' or
-        'jastrow_p' (-1: autotune)."""
+        'jastrow_p' (-1: autotune; 'jastrow_p' has fewer tiles and starts again
+        from its first past the last)."""
         self._check(self._lib.qmk_set_tile(self._h, KERNEL_CLASSES.index(kernel), int(tile)))
 
     def _out(self, out, shape, dtype):

@@ -228,7 +228,9 @@ std::vector<size_t> curve_order(const std::vector<double>& nucl) {
 // a tile meets those within r of it.  7500 AOs, 63,000 points, B = 24: four
 // classes, and a 256-point tile visits 0.12 of its K steps, 0.27 with the rows
 // in the caller's order, where nearly every step holds a diffuse shell;
-// BF16x3 forward pass 2.5 ms, 4.2 ms in the caller's order.
+// BF16x3 forward pass 2.5 ms, 4.2 ms in the caller's order.  The reach is taken at
+// an exponent argument of 25 whatever the precision parameter is (its cutoff is
+// 15.9 at B = 24 and 36.0 at B = 53); results do not depend on it.
 // Only the places depend on the nuclei: what the basis decides is kept
 // (RowPlan), so that a new geometry sorts its nuclei and no shells.
 void make_row_plan(qmk_ctx ctx) {
@@ -2022,8 +2024,8 @@ qmk_status qmk_mo_vgl_adjoint(qmk_ctx ctx, const void* w, int32_t w_dtype, doubl
       const int64_t resident = static_cast<int64_t>(std::max(1, ncu)) *
                                gemm_persist_blocks_per_cu(GemmKind::kDcoef, prec, cfg, w32, 0);
       // at least 256 points each, or 64 where that leaves CUs without work
-      // (water's 1280 points: 25 workgroups of 256 points took 28 us, 100 of 64
-      // take 7)
+      // (1280 points of the 25-AO molecule: 25 workgroups of 256 points took 28 us,
+      // 100 of 64 take 13 on the same tile and 5.6 on 64 x 32)
       const int64_t idle = std::min<int64_t>((P + 63) / 64, std::max(1, ncu) / (tiles * 5));
       int64_t ns = std::max<int64_t>(1, 4 * resident / (tiles * 5));
       ns = std::min<int64_t>(ns, std::max<int64_t>((P + 255) / 256, idle));

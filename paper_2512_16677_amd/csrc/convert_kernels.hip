@@ -61,8 +61,8 @@ __global__ __launch_bounds__(256) void pad_rows_batch_kernel(const PadJob* __res
 // W[p][c][n] -> hi, lo planes [Pp][5][Nw]: hi = bf16(x), lo = bf16(x - hi) of
 // the FP32-rounded weight x (round to nearest even); zeros beyond P and N.
 // Bound by memory.  With eight loads of one weight where rows were not 16-byte
-// aligned, and a search for the job by every thread, the batch of 96 molecules
-// took 6.44 ms, 6.25 since.
+// aligned, and a search for the job by every thread, a batch of 48 molecules took
+// 6.44 ms, 6.25 since.
 // One thread per eight consecutive n of one (p, c) row: idx < Pp * 5 * Nw / 8,
 // which the launchers keep below 2^32 (32-bit index arithmetic).
 template <typename T>

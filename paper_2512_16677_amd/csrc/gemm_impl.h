@@ -661,8 +661,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_persist(const GemmArgs* _
 
 // Tile configurations offered to the autotuner: {WGM, WGN, TM, TN, BK}.
 // 64 x 64 and 64 x 32 serve small products (1280 points of the 25-AO molecule:
-// forward product 9.8 us on 128 x 96, 4.2 us on 64 x 32, which fills 100 CUs
-// instead of 50); the 112-wide ones waste less of a column count just below a
+// forward product 9.0 us on 128 x 96 with 50 workgroups, 7.6 us on 64 x 160 with 100,
+// 4.6 us on 64 x 32, which forms no padded columns); the 112-wide ones waste less of a column count just below a
 // multiple of 112 (211 occupied orbitals: 256 columns on 128-wide tiles, 224
 // here; FP64 density product of 785,603 points and 1085 AOs 6.80 -> 5.75 ms).
 #define QMK_TILE_LIST(X) \

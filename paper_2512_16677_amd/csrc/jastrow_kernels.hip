@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void een_g0_kernel(const double* __restrict__ 
   for (int k1 = 0; k1 < kMaxOrd - 1; ++k1) g0[p * (kMaxOrd - 1) + k1] = k1 < NORD - 1 ? g[k1] : 0.0;
 }
 
-// Block = (walker w, 16 electrons i); each wave takes 4 of them and its
+// Block = (walker w, 8 electrons i); each wave takes 2 of them and its
 // lanes run over the electrons j, whose coordinates are staged in LDS in
 // chunks.  Writes rt[w][i][j] = exp(-kappa r_ij), zero on the diagonal (and so
 // in its powers) and in the padding rows, and

@@ -23,9 +23,11 @@ constexpr int kGroupMaxAo = 120;
 // the caller's order (see order_rows).  Screened passes in the caller's order
 // and in this one: 600 AOs 304 and 277 us (BF16x3 forward), 1200 AOs 815 and
 // 644 (FP64 forward), 643 and 558 (BF16x3 forward), 1650 AOs 2782 and 2211
-// (FP32 gradient).  Dense products do not gain from it, and every new set of
-// nuclei has to be checked for a new order (about 0.05 ms, 2 % of an
-// optimisation step of the 800-AO molecule), so the smaller ones go without.
+// (FP32 gradient).  Dense products do not gain from it (they use it all the same,
+// because a screened result equals the dense one bit for bit), and nuclei that
+// change the order have the copies of C laid out again: step of set_nucleus and a
+// dense FP64 forward pass in the caller's order and in this one, 1200 AOs 169 and
+// 188 us, 2000 AOs 245 and 267.  So the smaller ones go without.
 constexpr int64_t kOrderRowsAo = 1024;
 constexpr int kPointPad = 256;      // points are padded to a multiple of this
 constexpr int kAoPad = 128;         // AOs (K) padded to a multiple of this
@@ -82,7 +84,7 @@ struct AoTables {
 // beside a handful of such chains.  So where the 64-point wavefronts do not
 // fill the chip four times over (4 SIMDs x 256 CUs x 4 = 4096), they get
 // workgroups of their own and shorter chains.  1280 points of the 25-AO molecule: AO
-// stage 19 us in one piece, 7.5 us split; AO adjoint 18 and 8.5 us.
+// stage 20.3 us in one piece, 7.3 us split; AO adjoint 19.4 and 8.1 us.
 struct AoSplit {
   int32_t block, nz;
 };

@@ -23,7 +23,9 @@ constexpr int kSortMaxKeys = kSortMaxNuclei;  // LDS histogram of one block
 // far to near for the next, so that the far points of neighbours, which see
 // more of the AOs around, share tiles.  7500 AOs, 63,000 points, B = 24: a
 // 128-point tile visits 0.097 of its K steps, 0.104 with one key per nucleus
-// (BF16x3 product 1.95 and 2.06 ms).  One key where four would not fit the tables.
+// (BF16x3 product 1.95 and 2.06 ms).  The radii suit electrons that spread by about
+// a bohr around their nuclei; others share tiles less well, with the same results.
+// One key where four would not fit the tables.
 constexpr int kRings = 4;
 int rings(int64_t P, int64_t n_nuc) {
   return n_nuc * kRings <= kSortMaxKeys && (P + 1023) / 1024 * n_nuc * kRings <= (int64_t(1) << 22) ? kRings : 1;
